@@ -182,28 +182,17 @@ RLX_HD void mul576(const uint32_t (&x)[NW], const uint32_t (&y)[NW], uint32_t (&
 // in 576 bits, then the final comparison with m.  Each fold is an add-with-
 // carry chain (adding H 2^240, i.e. H << 16 from word 7 on) followed by a
 // subtract-with-borrow chain; every intermediate is non-negative.
-RLX_HD void mod_m(const uint32_t (&p)[2 * NW], uint32_t (&r)[NW]) {
-  // T1 = L + H 2^240 - H  (>= 0, < 2^817): 26 words
-  uint32_t t1[26];
-  {
-    uint32_t c = 0;
-#pragma unroll
-    for (int k = 0; k < 26; ++k) {
-      const uint32_t l = k < NW ? p[k] : 0u;
-      uint32_t hs = 0;  // word k of H << 240
-      if (k >= 7) {
-        const uint32_t hi = (k - 7 < NW) ? p[NW + k - 7] : 0u;
-        const uint32_t lo = (k >= 8 && k - 8 < NW) ? p[NW + k - 8] : 0u;
-        hs = (hi << 16) | (lo >> 16);
-      }
-      t1[k] = k < 7 ? l : addc(l, hs, c);
-    }
-    uint32_t br = 0;
-#pragma unroll
-    for (int k = 0; k < 26; ++k) t1[k] = subb(t1[k], k < NW ? p[NW + k] : 0u, br);
-  }
+
+// r = t mod m for t < 2^817 (26 words): the second fold and the rest.  Its
+// chains stop two words past what they add (word 16) and subtract (word 8); a
+// carry or borrow that runs further, or a top word that allows a result >= m
+// (together about 3 in 2^32), is finished in a branch, which is exact: 53
+// instructions fewer than running the chains, the third fold and the
+// comparison to the end for every product.
+RLX_HD void mod_m_folded(const uint32_t (&t1)[26], uint32_t (&r)[NW]) {
   // T2 = T1 mod 2^576 + T1hi 2^240 - T1hi, T1hi = words 18..25 (< 2^241):
-  // below 2^577, with the bit above 2^576 in t
+  // below 2^577, with the carry into word 17 and the borrow into word 9
+  // still to come
   uint32_t c = 0;
 #pragma unroll
   for (int k = 0; k < NW; ++k) {
@@ -213,23 +202,47 @@ RLX_HD void mod_m(const uint32_t (&p)[2 * NW], uint32_t (&r)[NW]) {
       const uint32_t lo = (k >= 8 && k - 8 < 8) ? t1[NW + k - 8] : 0u;
       hs = (hi << 16) | (lo >> 16);
     }
-    r[k] = k < 7 ? t1[k] : addc(t1[k], hs, c);
+    r[k] = (k < 7 || k == 17) ? t1[k] : addc(t1[k], hs, c);
   }
   uint32_t br = 0;
 #pragma unroll
-  for (int k = 0; k < NW; ++k) r[k] = subb(r[k], k < 8 ? t1[NW + k] : 0u, br);
-  const uint32_t t = c - br;  // T2 >= 0, so the borrow never exceeds the carry
-  // T3 = T2 mod 2^576 + t (2^240 - 1); when t = 1, T2 mod 2^576 < 2^482, so
-  // no further overflow; then < m
-  {
+  for (int k = 0; k < 9; ++k) r[k] = subb(r[k], k < 8 ? t1[NW + k] : 0u, br);
+  if ((c | br) != 0 || r[17] == 0xFFFFFFFFu) {
+    r[17] = addc(r[17], 0u, c);
+#pragma unroll
+    for (int k = 9; k < NW; ++k) r[k] = subb(r[k], 0u, br);
+    const uint32_t t = c - br;  // T2 >= 0, so the borrow never exceeds the carry
+    // T3 = T2 mod 2^576 + t (2^240 - 1); when t = 1, T2 mod 2^576 < 2^482, so
+    // no further overflow; then < m
     uint32_t cy = t << 16;
 #pragma unroll
     for (int k = 7; k < NW; ++k) r[k] = addc(r[k], 0u, cy);
     uint32_t b2 = t;
 #pragma unroll
     for (int k = 0; k < NW; ++k) r[k] = subb(r[k], 0u, b2);
+    canonicalize(r);
   }
-  canonicalize(r);
+}
+
+RLX_HD void mod_m(const uint32_t (&p)[2 * NW], uint32_t (&r)[NW]) {
+  // T1 = L + H 2^240 - H  (>= 0, < 2^817): 26 words
+  uint32_t t1[26];
+  uint32_t c = 0;
+#pragma unroll
+  for (int k = 0; k < 26; ++k) {
+    const uint32_t l = k < NW ? p[k] : 0u;
+    uint32_t hs = 0;  // word k of H << 240
+    if (k >= 7) {
+      const uint32_t hi = (k - 7 < NW) ? p[NW + k - 7] : 0u;
+      const uint32_t lo = (k >= 8 && k - 8 < NW) ? p[NW + k - 8] : 0u;
+      hs = (hi << 16) | (lo >> 16);
+    }
+    t1[k] = k < 7 ? l : addc(l, hs, c);
+  }
+  uint32_t br = 0;
+#pragma unroll
+  for (int k = 0; k < 26; ++k) t1[k] = subb(t1[k], k < NW ? p[NW + k] : 0u, br);
+  mod_m_folded(t1, r);
 }
 
 RLX_HD void mulmod_generic(const uint32_t (&x)[NW], const uint32_t (&y)[NW], uint32_t (&r)[NW]) {
