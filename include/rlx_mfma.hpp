@@ -103,6 +103,13 @@ __device__ __forceinline__ void mf_swap(uint32_t& a, uint32_t& b) {
   b = r[1];
 }
 
+// LDS writes of a wave become visible to the whole wave.
+__device__ __forceinline__ void mf_wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 typedef unsigned mf_v2u __attribute__((ext_vector_type(2)));
 
 // The 64-bit value with low word lo and high word hi (a register pair).
@@ -244,6 +251,310 @@ __device__ __forceinline__ void mfma_step_halves(uint32_t (&x)[NW], const Fetch0
 template <class Fetch>
 __device__ __forceinline__ void mfma_step(uint32_t (&x)[NW], const Fetch& fetch, bool force_general) {
   mfma_step_halves(x, fetch, fetch, force_general);
+}
+
+// ---------------------------------------------------------------------------
+// the step with contiguous output halves
+//
+// The same product with the output digits placed differently: A row
+// 32 mt + 8 q + 4 h + u is digit u of word 4 mt + q of the low half for h = 0
+// (words 0..8) and of the high half for h = 1 (words 9..18), so lanes 0..31
+// of a tile receive the low words of its states and lanes 32..63 the high
+// ones.  Each lane then carries through nine words of two states on its own,
+// and one exchange per word pair gives every lane its state: 10 exchanges and
+// 20 short chain links against 20 and 19 (v_permlane32_swap takes 8 cycles,
+// a link 16 with one multiply-add, 20 with five).  The carry into word 9 and
+// word 18 are joined after the exchange.  About 560 vector cycles per wave
+// against 720.
+constexpr int MF_SPLIT_STEPS = 17;  // step sizes 2^g with operands of this form: up to 65 536 lanes per record
+
+// Digit row of row `row` of output tile mt in this placement, or -1.
+RLX_HD constexpr int mf_split_row(int mt, int row) {
+  return ((row >> 2) & 1) == 0 ? (4 * mt + (row >> 3) < 9 ? 4 * (4 * mt + (row >> 3)) + (row & 3) : -1)
+                               : (4 * mt + (row >> 3) < 10 ? 4 * (9 + 4 * mt + (row >> 3)) + (row & 3) : -1);
+}
+
+// Next word of a signed carry chain over output rows: rows 4q .. 4q + 3 of a
+// tile (weights 2^0, 2^8, 2^16, 2^24) plus the carry c so far; returns the low
+// 32 bits and leaves the carry in c.  With |S| < 2^21, lo = S_0 + S_1 2^8 + c
+// and hi = S_2 + S_3 2^8 are below 2^30 in magnitude: two 32-bit shift-adds,
+// an add, and one multiply-add by an opaque 2^16.
+__device__ __forceinline__ uint32_t mf_chain(const mf_v16i& s, int q, int32_t k16, int32_t& c) {
+  const int32_t lo = (int32_t)((uint32_t)s[4 * q] + ((uint32_t)s[4 * q + 1] << 8)) + c;
+  const int32_t hi = (int32_t)((uint32_t)s[4 * q + 2] + ((uint32_t)s[4 * q + 3] << 8));
+  const int64_t w = (int64_t)hi * k16 + (int64_t)lo;
+  c = (int32_t)((uint64_t)w >> 32);
+  return (uint32_t)w;
+}
+
+// x + the pending carries of mfma_step_split, exact and canonical: p2, p9 and
+// p11 (-1, 0 or 1) at words 2, 9 and 11, and h2 (0 or -1, the upper half of a
+// negative word 18) with the weight of word 19's share of the fold.
+__device__ __forceinline__ void mf_settle(uint32_t (&x)[NW], int32_t p2, int32_t p9, int32_t p11, int32_t h2) {
+  int64_t acc = 0;
+#pragma unroll
+  for (int k = 0; k < NW; ++k) {
+    int64_t add = 0;
+    if (k == 1) add = -(int64_t)h2;
+    if (k == 2) add = p2;
+    if (k == 8) add = (int64_t)h2 * 65536;
+    if (k == 9) add = p9;
+    if (k == 11) add = p11;
+    acc += (int64_t)x[k] + add;
+    x[k] = (uint32_t)acc;
+    acc >>= 32;
+  }
+  // x + top 2^576 = x + top (2^240 - 1), top in {-1, 0, 1}; x is then so far
+  // from the other end that nothing passes 2^576 or 0 again
+  const int64_t top = acc;
+  acc = 0;
+#pragma unroll
+  for (int k = 0; k < NW; ++k) {
+    const int64_t add = k == 0 ? -top : k == 7 ? top * 65536 : 0;
+    acc += (int64_t)x[k] + add;
+    x[k] = (uint32_t)acc;
+    acc >>= 32;
+  }
+  canonicalize(x);
+}
+
+// X <- A X mod m with operands in the split placement: fetch0 for the states
+// of lanes 0..31, fetch1 for lanes 32..63.  Must run with all 64 lanes of the
+// wave active; returns the canonical residue; `force_general` sends the end
+// of it through its general branch.
+template <class Fetch0, class Fetch1>
+__device__ __forceinline__ void mfma_step_split(uint32_t (&x)[NW], const Fetch0& fetch0, const Fetch1& fetch1,
+                                                bool force_general) {
+  uint32_t a[9], b[9];
+#pragma unroll
+  for (int k = 0; k < 9; ++k) {
+    a[k] = x[k] ^ 0x80808080u;
+    b[k] = x[9 + k] ^ 0x80808080u;
+  }
+#pragma unroll
+  for (int k = 0; k < 9; ++k) mf_swap(a[k], b[k]);
+  const mf_v4i b0[3] = {mf_v4i{(int)a[0], (int)a[1], (int)a[2], (int)a[3]},
+                        mf_v4i{(int)a[4], (int)a[5], (int)a[6], (int)a[7]}, mf_v4i{(int)a[8], 1, 0, 0}};
+  const mf_v4i b1[3] = {mf_v4i{(int)b[0], (int)b[1], (int)b[2], (int)b[3]},
+                        mf_v4i{(int)b[4], (int)b[5], (int)b[6], (int)b[7]}, mf_v4i{(int)b[8], 1, 0, 0}};
+  const int32_t k16 = (int32_t)mf_opaque(65536u);
+  const mf_v16i zero = {};
+  int32_t c0 = 0, c1 = 0;  // carries of the two states' chains
+  uint32_t t0 = 0, t1 = 0;
+#pragma unroll
+  for (int mt = 0; mt < 3; ++mt) {
+    const mf_v4i f0 = fetch0(3 * mt), f1 = fetch0(3 * mt + 1), f2 = fetch0(3 * mt + 2);
+    const mf_v4i g0 = fetch1(3 * mt), g1 = fetch1(3 * mt + 1), g2 = fetch1(3 * mt + 2);
+    mf_v16i s0 = __builtin_amdgcn_mfma_i32_32x32x32_i8(f0, b0[0], zero, 0, 0, 0);
+    mf_v16i s1 = __builtin_amdgcn_mfma_i32_32x32x32_i8(g0, b1[0], zero, 0, 0, 0);
+    s0 = __builtin_amdgcn_mfma_i32_32x32x32_i8(f1, b0[1], s0, 0, 0, 0);
+    s1 = __builtin_amdgcn_mfma_i32_32x32x32_i8(g1, b1[1], s1, 0, 0, 0);
+    s0 = __builtin_amdgcn_mfma_i32_32x32x32_i8(f2, b0[2], s0, 0, 0, 0);
+    s1 = __builtin_amdgcn_mfma_i32_32x32x32_i8(g2, b1[2], s1, 0, 0, 0);
+#pragma unroll
+    for (int q = 0; q < (mt < 2 ? 4 : 2); ++q) {
+      const int j = 4 * mt + q;
+      uint32_t w0 = mf_chain(s0, q, k16, c0), w1 = mf_chain(s1, q, k16, c1);
+      mf_swap(w0, w1);
+      if (j < 9) {
+        x[j] = w0;
+        x[9 + j] = w1;
+      } else {
+        t0 = w0;  // the carry out of the low half
+        t1 = w1;  // word 18
+      }
+    }
+    // the first tile's words before the last tile's MFMAs: 120 VGPRs in the
+    // staged generate kernels against 128 and spills for normals
+    if (mt == 0) __builtin_amdgcn_sched_barrier(0);
+  }
+  // t0 (signed) enters at word 9, t1 = h (< 2^15) is folded with 2^576 =
+  // 2^240 - 1: - h at word 0, + (h << 16) at word 7.  Each sum is carried two
+  // words; what runs further (p2, p9, p11), or a top word that allows a
+  // result >= m, is settled in the rare branch.
+  uint32_t br = 0, cy = 0, cf = 0;
+  const uint32_t sgn = (uint32_t)((int32_t)t0 >> 31);
+  x[0] = subb(x[0], t1, br);
+  x[1] = subb(x[1], 0u, br);
+  x[7] = addc(x[7], t1 << 16, cy);
+  x[8] = addc(x[8], t1 >> 16, cy);
+  x[9] = addc(x[9], t0, cf);
+  x[10] = addc(x[10], sgn, cf);
+  const uint32_t p11 = cf + sgn;
+  if ((br | cy | p11) != 0 || x[17] == 0xFFFFFFFFu || force_general)
+    mf_settle(x, -(int32_t)br, (int32_t)cy, (int32_t)p11, (int32_t)t1 >> 31);
+}
+
+template <class Fetch>
+__device__ __forceinline__ void mfma_step_split(uint32_t (&x)[NW], const Fetch& fetch, bool force_general) {
+  mfma_step_split(x, fetch, fetch, force_general);
+}
+
+// ---------------------------------------------------------------------------
+// product by a factor that 32 lanes share
+//
+// Y <- X Y mod m with one X per half-wave and a Y of each lane's own: the
+// lanes of a record start this way (X the record's state, Y = A^l).  The
+// digits of the product are a contraction too, with the Toeplitz matrix of
+// X's digits, P_r = sum_i x_{r-i} y_i, as the A operand:
+//
+//  * X and Y enter as balanced base-256 digits, 72 and a last one in {0, 1}:
+//    the bytes of X + 0x8080...80 with their top bits flipped, and the carry
+//    out of that sum;
+//  * Y's digits are placed as the step places them (halves exchanged across
+//    the lane halves), and the output rows as mfma_step_split places them:
+//    lanes 0..31 receive words 0..17 of the product, lanes 32..63 words
+//    18..35.  Lane (rr, h) = (l mod 32, l div 32) of the A operand for output
+//    tile mt and input step ks then holds x_{r - 16 ks - 36 h - j}, j < 16,
+//    for the row r = 16 mt + 4 (rr div 8) + rr mod 4 + 72 (rr div 4 mod 2):
+//    seven windows d = mt - ks = -2..4 of X's digits in reversed order, bytes
+//    151 - r + 16 mt - 16 d + 36 h and up of an array Z that holds digit q at
+//    151 - q between zeros (the digit y_72 falls on byte 4 of step 2 of the
+//    upper half by itself);
+//  * the windows start at any byte, and LDS reads that are not word-aligned
+//    run at a fraction of the rate (start-up 20% slower than mulmod_generic
+//    with them, 20% faster without), so Z is kept four times, copy c shifted
+//    down by 3 - c bytes, and lane rr reads whole words of copy rr mod 4;
+//  * |P_r| <= 73 128 128 < 2^21, and the 36 words of the product follow by
+//    the step's chain and are reduced by mod_m.
+constexpr int MF_SHARED_COPY = 320;                  // bytes between copies (bank offset 16)
+constexpr int MF_SHARED_BYTES = 4 * MF_SHARED_COPY;  // per half-wave
+// The B operands of one tile of 32 lanes in memory: 3 steps x 64 lanes x 16
+// bytes; a level's table holds the two tiles of Y = A^l, l < 64.
+constexpr size_t MF_START_WORDS = (size_t)2 * 3 * 64 * 4;
+
+// Bytes of x + 0x8080...80 with the top bits flipped: digits 0..71; returns
+// digit 72.
+__device__ __forceinline__ uint32_t mf_balance(const uint32_t (&x)[NW], uint32_t (&d)[NW]) {
+  uint32_t c = 0;
+#pragma unroll
+  for (int k = 0; k < NW; ++k) d[k] = addc(x[k], 0x80808080u, c) ^ 0x80808080u;
+  return c;
+}
+
+// The shared factor's digits to LDS, each half-wave its own X at lds + h
+// MF_SHARED_BYTES: lane rr < 18 of a half holds word rr of X, the others 0.
+// The carries of X + 0x8080...80 come from one add of the wave's generate and
+// propagate masks, so no lane runs an 18-word chain.  Words 0..57 of each
+// copy are written: all that the windows cover.
+__device__ __forceinline__ void mf_shared_digits(uint32_t w, uint8_t* __restrict__ lds, uint32_t lane) {
+  const uint32_t rr = lane & 31u, h = lane >> 5;
+  const uint64_t gen = __ballot(w > 0x7F7F7F7Fu), prop = __ballot(w == 0x7F7F7F7Fu);
+  const uint64_t carry = ((gen | prop) + gen) ^ prop;
+  // word 37 - rr of Z; lane 18 holds digit 72, lanes above it zero digits
+  const uint32_t z =
+      __builtin_bswap32((w + 0x80808080u + ((uint32_t)(carry >> lane) & 1u)) ^ 0x80808080u);
+  const uint32_t up = __builtin_amdgcn_update_dpp(0, z, 0x138, 0xF, 0xF, true);  // wave_shr:1: word 38 - rr
+  uint32_t* const base = reinterpret_cast<uint32_t*>(lds + h * MF_SHARED_BYTES);
+#pragma unroll
+  for (uint32_t c = 0; c < 4; ++c) {
+    uint32_t* const copy = base + c * (MF_SHARED_COPY / 4);
+    copy[37u - rr] = __builtin_amdgcn_alignbyte(up, z, 3u - c);
+    if (rr < 26) copy[rr < 6 ? rr : 32u + rr] = 0u;
+  }
+  mf_wave_sync();
+}
+
+// B operands of the lanes' own factors y: b[0..2] of state tile 0 (lanes
+// 0..31), b[3..5] of tile 1.
+__device__ __forceinline__ void mf_shared_operands(const uint32_t (&y)[NW], mf_v4i (&b)[6]) {
+  uint32_t lo[9], hi[9], d[NW];
+  uint32_t l9 = 0, h9 = mf_balance(y, d);
+#pragma unroll
+  for (int k = 0; k < 9; ++k) {
+    lo[k] = d[k];
+    hi[k] = d[9 + k];
+  }
+#pragma unroll
+  for (int k = 0; k < 9; ++k) mf_swap(lo[k], hi[k]);
+  mf_swap(l9, h9);
+  b[0] = mf_v4i{(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3]};
+  b[1] = mf_v4i{(int)lo[4], (int)lo[5], (int)lo[6], (int)lo[7]};
+  b[2] = mf_v4i{(int)lo[8], (int)l9, 0, 0};
+  b[3] = mf_v4i{(int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
+  b[4] = mf_v4i{(int)hi[4], (int)hi[5], (int)hi[6], (int)hi[7]};
+  b[5] = mf_v4i{(int)hi[8], (int)h9, 0, 0};
+}
+
+// r = X Y mod m from the digits that mf_shared_digits wrote and the operands
+// of mf_shared_operands (ONE: both halves have the same X).  Must run with
+// all 64 lanes of the wave active.
+template <bool ONE>
+__device__ __forceinline__ void mf_shared_product(const uint8_t* __restrict__ lds, const mf_v4i (&b)[6],
+                                                  uint32_t (&r)[NW], uint32_t lane) {
+  const uint32_t rr = lane & 31u, h = lane >> 5;
+  // lane (rr, h)'s window d in its copy: bytes 0..231 for d = -2..4
+  const uint8_t* f0 = lds + ((rr & 3u) * MF_SHARED_COPY + 148u - 4u * (rr >> 3) - 72u * ((rr >> 2) & 1u) + 36u * h - 64u);
+  typedef uint32_t words4 __attribute__((ext_vector_type(4), aligned(4)));
+  auto window = [&](int half, int d) {
+    return __builtin_bit_cast(mf_v4i, *reinterpret_cast<const words4*>(f0 + half * MF_SHARED_BYTES + 16 * (4 - d)));
+  };
+  const int32_t k16 = (int32_t)mf_opaque(65536u);
+  // the first fold of mod_m word by word as the two halves L and H arrive:
+  // T1 = L + H 2^240 - H
+  uint32_t t[26], hw[NW];
+  uint32_t cy = 0, br = 0;
+  int32_t c0 = 0, c1 = 0;
+  uint32_t e0 = 0, e1 = 0;
+#pragma unroll
+  for (int mt = 0; mt < 5; ++mt) {
+    mf_v16i s0 = {}, s1 = {};
+#pragma unroll
+    for (int ks = 0; ks < 3; ++ks) {
+      const mf_v4i f = window(0, mt - ks);
+      s0 = __builtin_amdgcn_mfma_i32_32x32x32_i8(f, b[ks], s0, 0, 0, 0);
+      s1 = __builtin_amdgcn_mfma_i32_32x32x32_i8(ONE ? f : window(1, mt - ks), b[3 + ks], s1, 0, 0, 0);
+    }
+#pragma unroll
+    for (int q = 0; q < (mt < 4 ? 4 : 2); ++q) {
+      const int j = 4 * mt + q;
+      uint32_t w0 = mf_chain(s0, q, k16, c0), w1 = mf_chain(s1, q, k16, c1);
+      mf_swap(w0, w1);
+      hw[j] = w1;
+      if (j >= 7) w0 = addc(w0, j == 7 ? hw[0] << 16 : __builtin_amdgcn_alignbit(hw[j - 7], hw[j - 8], 16), cy);
+      t[j] = subb(w0, w1, br);
+    }
+    if (mt == 4) {
+      // with row 144 (x_72 y_72) a high half carries nothing past word 35
+      e0 = (uint32_t)(c0 + s0[8]);
+      e1 = (uint32_t)(c1 + s1[8]);
+    }
+    // one tile's words before the next tile's MFMAs: fits the generate
+    // kernels' 128 VGPRs
+    __builtin_amdgcn_sched_barrier(0);
+  }
+#pragma unroll
+  for (int k = NW; k < 26; ++k) {
+    const uint32_t w = addc(k < 25 ? __builtin_amdgcn_alignbit(hw[k - 7], hw[k - 8], 16) : hw[17] >> 16, 0u, cy);
+    t[k] = subb(w, 0u, br);
+  }
+  // H lacks the carry `low` out of L, and has one of its own, `high`, only
+  // when that addition would wrap: T1 += (low + high 2^576) (2^240 - 1)
+  uint32_t low = (uint32_t)c0, other = (uint32_t)c1, b2 = 0, c9 = 0;
+  mf_swap(low, other);
+  mf_swap(e0, e1);
+  const uint32_t high = e1;
+  const uint32_t sgn = (uint32_t)((int32_t)low >> 31);
+  t[0] = subb(t[0], low, b2);
+  t[1] = subb(t[1], sgn, b2);
+  t[7] = addc(t[7], low << 16, c9);
+  t[8] = addc(t[8], (uint32_t)((int32_t)low >> 16), c9);
+  const int32_t p2 = -(int32_t)(b2 + sgn), p9 = (int32_t)(c9 + sgn);
+  if ((p2 | p9 | (int32_t)high) != 0) {
+    int64_t acc = 0;
+#pragma unroll
+    for (int k = 0; k < 26; ++k) {
+      int64_t add = 0;
+      if (k == 2) add = p2;
+      if (k == 9) add = p9;
+      if (k == 18) add = -(int64_t)(int32_t)high;
+      if (k == 25) add = (int64_t)(int32_t)high * 65536;
+      acc += (int64_t)t[k] + add;
+      t[k] = (uint32_t)acc;
+      acc >>= 32;
+    }
+  }
+  mod_m_folded(t, r);
 }
 
 }  // namespace rlx

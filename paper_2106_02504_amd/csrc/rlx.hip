@@ -175,23 +175,36 @@ __global__ __launch_bounds__(64) void k_tab_mf_k(const uint32_t* __restrict__ cw
 }
 
 // The A operands: lane l of fragment f = 3 mt + ks of level g holds, in its
-// 16 bytes j, the digit of output row 32 mt + (l mod 32) of the input column
-// mf_input_column(l div 32, ks, j), zero for a zero column.
+// 16 bytes j, the digit of output row 32 mt + (l mod 32), or SPLIT of digit
+// row mf_split_row(mt, l mod 32), of the input column mf_input_column(l div
+// 32, ks, j), zero for a zero column or row.
+template <bool SPLIT>
 __global__ __launch_bounds__(64) void k_tab_mf_frag(const int8_t* __restrict__ bal, uint32_t* __restrict__ M,
                                                     int rows) {
   const int t = blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= rows * MF_FRAGS * 64) return;
   const int g = t / (MF_FRAGS * 64), f = (t / 64) % MF_FRAGS, l = t % 64;
-  const int mt = f / 3, ks = f % 3, h = l / 32, row = 32 * mt + l % 32;
+  const int mt = f / 3, ks = f % 3, h = l / 32, row = SPLIT ? mf_split_row(mt, l % 32) : 32 * mt + l % 32;
   for (int q = 0; q < 4; ++q) {
     uint32_t word = 0;
     for (int b = 0; b < 4; ++b) {
       const int col = mf_input_column(h, ks, 4 * q + b);
-      const int8_t v = col < 0 ? (int8_t)0 : bal[((size_t)g * MF_COLS + col) * MF_ROWS + row];
+      const int8_t v = col < 0 || row < 0 ? (int8_t)0 : bal[((size_t)g * MF_COLS + col) * MF_ROWS + row];
       word |= (uint32_t)(uint8_t)v << (8 * b);
     }
     M[(size_t)t * 4 + q] = word;
   }
+}
+
+// B operands of the lane start-up (mf_shared_operands) for Y = A_p^l, l < 64:
+// one wave, lane l its own l.
+__global__ __launch_bounds__(64) void k_tab_start(const uint32_t* __restrict__ W, uint32_t* __restrict__ S) {
+  uint32_t y[NW];
+  load_words(W + (size_t)threadIdx.x * NW, y);
+  mf_v4i b[6];
+  mf_shared_operands(y, b);
+#pragma unroll
+  for (int k = 0; k < 6; ++k) reinterpret_cast<mf_v4i*>(S)[64 * k + threadIdx.x] = b[k];
 }
 
 // ---------------------------------------------------------------------------
@@ -342,6 +355,66 @@ __global__ __launch_bounds__(BLOCK) void k_skip_levels(rlx_state* __restrict__ s
 // ---------------------------------------------------------------------------
 // generation (sections 2.1-2.3)
 
+// Word rr of record i (0 from word 18 on) and the record's position and
+// level, for a half-wave whose lanes share the record; without a record
+// (active false) the state 1.
+__device__ __forceinline__ uint32_t load_record_word(const rlx_state* __restrict__ st, uint64_t i, bool active,
+                                                     uint32_t rr, uint32_t& pos, uint32_t& p) {
+  uint32_t w = rr == 0 ? 1u : 0u;
+  if (active) {
+    const uint32_t* const r = reinterpret_cast<const uint32_t*>(st + i);
+    if (rr < NW) w = r[rr];
+    const uint2 v = *reinterpret_cast<const uint2*>(r + NW);
+    pos = v.x;
+    p = v.y;
+  }
+  return w;
+}
+
+// check_record for a half-wave that holds the record's words one per lane
+// (w): X >= m needs words 8..17 all ones, and only then is the record
+// compared with m.
+__device__ __forceinline__ uint32_t check_record_word(const rlx_state* __restrict__ st, uint64_t i, uint32_t w,
+                                                      uint32_t pos, uint32_t sp, uint32_t p) {
+  uint32_t bad = 0;
+  if (sp != p) bad |= RLX_ERR_BAD_P;
+  if (pos > 11) bad |= RLX_ERR_BAD_POS;
+  const uint64_t ones = __ballot(w == 0xFFFFFFFFu) >> (threadIdx.x & 32u);
+  if ((ones & 0x3FF00u) == 0x3FF00u) {
+    uint32_t x[NW], a, b;
+    load_record(st, i, x, a, b);
+    if (geq_m(x)) bad |= RLX_ERR_BAD_X;
+  }
+  return bad;
+}
+
+// X_l = A^l X_0 for lane l of records whose lanes fill half-waves (G >= 32),
+// X_0's word rr in lane rr of each half (mf_shared_product).  The factors A^l
+// are ready-made operands for l < 64; for larger G (one wave of a record's
+// many) they are built from the window table.  About 390 vector instructions
+// per wave; with one generic product per lane (890) seeding and drawing
+// 65 536 streams x 4096 doubles took 407 us against 398, 5000 x 1001 at 32
+// lanes 16.7 us against 14.5, and one stream of 2^20 doubles 14.2 us against
+// 13.0.
+template <int LGS>
+__device__ __forceinline__ void start_shared(uint32_t (&x)[NW], uint32_t w, uint32_t l, uint32_t lg,
+                                             const uint32_t* __restrict__ S, const uint32_t* __restrict__ W,
+                                             uint8_t* __restrict__ lds, uint32_t lane) {
+  mf_v4i b[6];
+  if (LGS == 6 && lg > 6) {
+    uint32_t y[NW];
+    load_words(W + (size_t)l * NW, y);
+    mf_shared_operands(y, b);
+  } else {
+    const mf_v4i* const s = reinterpret_cast<const mf_v4i*>(S) + lane;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) b[k] = s[64 * (LGS == 6 ? k : k % 3)];
+  }
+  mf_shared_digits(w, lds, lane);
+  mf_shared_product<LGS == 6>(lds, b, x, lane);
+  wave_sync();
+}
+
 // Draw `count` values for every record with G = 2^lg lanes per record.
 //
 // Block t of a record is the t-th LCG state visited (t = 0 is the state on
@@ -370,7 +443,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(K == Out:
                                                     uint64_t* __restrict__ trace, uint64_t trace_steps,
                                                     const uint32_t* __restrict__ ctabs,
                                                     const uint32_t* __restrict__ mtabs,
-                                                    const uint32_t* __restrict__ W, uint32_t lg,
+                                                    const uint32_t* __restrict__ W,
+                                                    const uint32_t* __restrict__ S, uint32_t lg,
                                                     uint32_t p, uint32_t* __restrict__ err,
                                                     int force_general, int writeback) {
   // Per-lane state kept across the loop is x plus four 32-bit words (record
@@ -387,26 +461,48 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(K == Out:
   const uint32_t l = (uint32_t)tid & ((1u << lg) - 1u);
   const bool force = force_general != 0;
 
+  // SHARED: the lanes of a half-wave belong to one record and start together
+  // from its digits (start_shared); otherwise each lane loads the record and
+  // multiplies by its own A^l
+  constexpr bool SHARED = MF && LGS >= 5;
   uint32_t x[NW];
   uint32_t pos = 0, sp = 0;
   bool active = (tid >> lg) < n;
-  if (active) {
-    load_record(st, i, x, pos, sp);
-    const uint32_t bad = check_record(x, pos, sp, p);
-    if (bad) {
-      if (l == 0) atomicOr(err, bad);
-      active = false;
+  uint32_t w = 0;
+  if constexpr (SHARED) {
+    w = load_record_word(st, i, active, threadIdx.x & 31u, pos, sp);
+    if (active) {
+      const uint32_t bad = check_record_word(st, i, w, pos, sp, p);
+      if (bad) {
+        if (l == 0) atomicOr(err, bad);
+        active = false;
+      }
     }
-  }
-  if (!active) {
-    set_one(x);
-    pos = 0;
+    if (!active) pos = 0;
+  } else {
+    if (active) {
+      load_record(st, i, x, pos, sp);
+      const uint32_t bad = check_record(x, pos, sp, p);
+      if (bad) {
+        if (l == 0) atomicOr(err, bad);
+        active = false;
+      }
+    }
+    if (!active) {
+      set_one(x);
+      pos = 0;
+    }
   }
   const uint32_t nadv = (uint32_t)((pos + count) / FIELDS);
 
   // lane l starts at block l: X_l = A^l X_0 (bits 6 and up of l are the
   // same for the whole wave)
-  if (STAGED) skip_windows(x, l, W);
+  if constexpr (SHARED) {
+    uint8_t* const lds = reinterpret_cast<uint8_t*>(stage + (size_t)(threadIdx.x & ~63u) * SLOT_VALUES);
+    start_shared<LGS>(x, w, l, lg, S, W, lds, threadIdx.x & 63u);
+  } else if (STAGED) {
+    skip_windows(x, l, W);
+  }
   const uint32_t* __restrict__ ctab = ctabs + (size_t)lg * FOLD_ROW_WORDS;
   // MF: the step's matrix-core A operands for A^G, staged in LDS once per
   // block (9 KB) and read by every step
@@ -447,7 +543,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(K == Out:
     }
     if (__any(live && t + (1u << lg) <= nadv)) {
       if constexpr (MF) {
-        mfma_step(x, MfFromArray{af, threadIdx.x & 63}, force);
+        mfma_step_split(x, MfFromArray{af, threadIdx.x & 63}, force);
       } else {
         step(x, constant_table(ctab), force, SgprBarrier());
       }
@@ -531,10 +627,10 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(K == Out:
     if (__any(live && t + (1u << lg) <= nadv)) {
       if (uniform && u0 == u1) {
         // one level for the wave: one operand fetch serves both halves
-        mfma_step(x, MfFromBuffer(level_ptr(L.M, u0) + (size_t)lg * MF_LEVEL_WORDS, threadIdx.x & 63), false);
+        mfma_step_split(x, MfFromBuffer(level_ptr(L.M, u0) + (size_t)lg * MF_LEVEL_WORDS, threadIdx.x & 63), false);
       } else if (uniform) {
-        mfma_step_halves(x, MfFromBuffer(level_ptr(L.M, u0) + (size_t)lg * MF_LEVEL_WORDS, threadIdx.x & 63),
-                         MfFromBuffer(level_ptr(L.M, u1) + (size_t)lg * MF_LEVEL_WORDS, threadIdx.x & 63), false);
+        mfma_step_split(x, MfFromBuffer(level_ptr(L.M, u0) + (size_t)lg * MF_LEVEL_WORDS, threadIdx.x & 63),
+                        MfFromBuffer(level_ptr(L.M, u1) + (size_t)lg * MF_LEVEL_WORDS, threadIdx.x & 63), false);
       } else if (active) {
         uint32_t a[NW];
         load_words(level_ptr(L.C, li) + (size_t)lg * FOLD_ROW_WORDS, a);  // C_0 = A^G
@@ -641,7 +737,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MF ? 4 : 
     wave_sync();
     if (__any(live && t + (1u << lg) <= nadv)) {
       if constexpr (MF) {
-        mfma_step(x, MfFromArray{af, threadIdx.x & 63}, false);
+        mfma_step_split(x, MfFromArray{af, threadIdx.x & 63}, false);
       } else {
         step(x, constant_table(ctab), false, SgprBarrier());
       }
@@ -891,7 +987,7 @@ void launch_table_build(uint32_t p, int rows, uint32_t* T, uint32_t* C, uint32_t
   k_tab_win<<<(WIN_ROWS * WIN_COLS + 63) / 64, 64, 0, s>>>(T, W);
   k_tab_mf_c<<<(rows * MF_BYTES + 63) / 64, 64, 0, s>>>(T, cw, bal, rows);
   k_tab_mf_k<<<(rows + 63) / 64, 64, 0, s>>>(cw, bal, rows);
-  k_tab_mf_frag<<<rows * MF_FRAGS, 64, 0, s>>>(bal, M, rows);
+  k_tab_mf_frag<false><<<rows * MF_FRAGS, 64, 0, s>>>(bal, M, rows);
 }
 
 int tables(uint32_t p, hipStream_t s, Tables* out) {
@@ -921,11 +1017,15 @@ int tables(uint32_t p, hipStream_t s, Tables* out) {
     (void)hipFree(t.T);
     (void)hipFree(t.C);
     (void)hipFree(t.W);
+    (void)hipFree(t.S);
+    (void)hipFree(t.P);
     (void)hipFree(t.M);
     (void)hipFree(cw);
     (void)hipFree(bal);
   };
   if (hipMalloc(&t.W, WIN_WORDS * sizeof(uint32_t)) != hipSuccess ||
+      hipMalloc(&t.S, MF_START_WORDS * sizeof(uint32_t)) != hipSuccess ||
+      hipMalloc(&t.P, (size_t)MF_SPLIT_STEPS * MF_LEVEL_WORDS * sizeof(uint32_t)) != hipSuccess ||
       hipMalloc(&t.M, (size_t)FOLD_G * MF_LEVEL_WORDS * sizeof(uint32_t)) != hipSuccess ||
       hipMalloc(&cw, (size_t)FOLD_G * MF_BYTES * NW * sizeof(uint32_t)) != hipSuccess ||
       hipMalloc(&bal, (size_t)FOLD_G * MF_COLS * MF_ROWS) != hipSuccess) {
@@ -933,6 +1033,8 @@ int tables(uint32_t p, hipStream_t s, Tables* out) {
     return RLX_ENOMEM;
   }
   launch_table_build(p, FOLD_G, t.T, t.C, t.W, t.M, cw, bal, s);
+  k_tab_mf_frag<true><<<MF_SPLIT_STEPS * MF_FRAGS, 64, 0, s>>>(bal, t.P, MF_SPLIT_STEPS);
+  k_tab_start<<<1, 64, 0, s>>>(t.W, t.S);
   if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess) {
     release();
     return RLX_EHIP;
@@ -1037,7 +1139,7 @@ int level_set(LevelSet* L) {
     if (L->n == (uint32_t)MAX_RECORD_LEVELS) return RLX_EINVAL;
     L->p[L->n] = kv.first.second;
     L->C[L->n] = kv.second.C;
-    L->M[L->n] = kv.second.M;
+    L->M[L->n] = kv.second.P;
     L->W[L->n] = kv.second.W;
     ++L->n;
   }
@@ -1104,10 +1206,10 @@ int generate_impl(rlx_state* states, uint64_t n, uint64_t count, void* out, uint
   case L:                                                                                             \
     if (mf) {                                                                                         \
       k_generate<K, TRACE, L, true><<<grid, BLOCK, 0, s>>>(states, (uint32_t)n, count, o, trace, trace_steps, t.C, \
-                                                            t.M, t.W, lg, p, err, force_general, writeback); \
+                                                            t.P, t.W, t.S, lg, p, err, force_general, writeback); \
     } else {                                                                                          \
       k_generate<K, TRACE, L, false><<<grid, BLOCK, 0, s>>>(states, (uint32_t)n, count, o, trace, trace_steps, t.C, \
-                                                             t.M, t.W, lg, p, err, force_general, writeback); \
+                                                             t.P, t.W, t.S, lg, p, err, force_general, writeback); \
     }                                                                                                 \
     break;
   switch (lgs) {
@@ -1136,7 +1238,7 @@ int generate_lcg52_impl(rlx_state* states, uint64_t n, uint64_t count, double* o
 #define RLX_GEN52(L)                                                                                        \
   case L:                                                                                                   \
     if (mf) {                                                                                               \
-      k_generate_lcg52<L, true><<<grid, BLOCK, 0, s>>>(states, (uint32_t)n, count, out, t.C, t.M, t.W, lg, p, \
+      k_generate_lcg52<L, true><<<grid, BLOCK, 0, s>>>(states, (uint32_t)n, count, out, t.C, t.P, t.W, lg, p, \
                                                        err, writeback);                                     \
     } else {                                                                                                \
       k_generate_lcg52<L, false><<<grid, BLOCK, 0, s>>>(states, (uint32_t)n, count, out, t.C, t.M, t.W, lg,  \

@@ -175,7 +175,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MF ? 3 : 
         group_store<LGS>(stage, tid_blk, l, u0, span, active, base);
         if (__any(live && t + G < nblocks)) {
           if constexpr (MF) {
-            mfma_step(x, fetch, false);
+            mfma_step_split(x, fetch, false);
           } else {
             step(x, constant_table(ctab), false, SgprBarrier());
           }
@@ -324,7 +324,7 @@ int upload(rlx_plan* plan, const Planned& pl, hipStream_t s) {
     if (rc) return rc;
     hd.C[k] = t.C;
     hd.W[k] = t.W;
-    hd.M[k] = t.M;
+    hd.M[k] = t.P;
     hd.p[k] = pl.ps[k];
   }
   // the previous upload must have left the staging buffers

@@ -16,6 +16,8 @@ struct Tables {
   uint32_t* C = nullptr;  // FOLD_WORDS words
   uint32_t* W = nullptr;  // WIN_WORDS words
   uint32_t* M = nullptr;  // RLX_FOLD_G * MF_LEVEL_WORDS words: matrix-core step operands
+  uint32_t* P = nullptr;  // MF_SPLIT_STEPS * MF_LEVEL_WORDS words: the same, output halves contiguous
+  uint32_t* S = nullptr;  // MF_START_WORDS words: lane start-up operands
 };
 
 inline hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s); }
