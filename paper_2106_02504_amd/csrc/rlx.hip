@@ -551,6 +551,144 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(K == Out:
   }
 }
 
+// One lane per record (G = 1): for many records with few values each, where a
+// lane start-up would cost more than the steps.  What bounds it is memory:
+// 80-byte records read and written and rows of a few hundred bytes.  A wave's
+// 64 records and, for each step, its 64 x 96 bytes of values pass through LDS
+// so that each instruction moves consecutive addresses: records as one run of
+// 5120 bytes (one lane per record would touch 40 lines in each of five
+// instructions), values as the 96-byte runs of consecutive rows, which the L2
+// joins to whole lines as the next step's runs follow (plain stores).  When
+// all records of the wave have one even position and rows are 16-byte
+// aligned, values go out in pairs, otherwise one by one.  2^19 records x 24
+// doubles over three sets of buffers: 43 us (4.3 TB/s) against 90 with one
+// lane storing its own row value by value; 2^20 x 12: 46 us against 109.  A
+// record's two steps (192 bytes) are kept before storing from 13 values on
+// (T = 2, 51 us instead of 65 at 24 values before rows were kept whole); with
+// up to 12 the smaller stage (T = 1) leaves twice the waves (2^20 x 12: 63 us
+// against 80).  Rows that end within the kept steps go out as the one run of
+// whole lines they are, for any count and positions.
+constexpr uint64_t ROWS_MAX_COUNT = 1ull << 20;  // 32-bit byte offsets within a wave's 64 rows
+
+template <Out K, uint32_t T>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(T == 1 ? 4 : 2))) void k_generate_rows(
+    rlx_state* __restrict__ st, uint32_t n, uint32_t count, uint64_t* __restrict__ out,
+    const uint32_t* __restrict__ mtabs, uint32_t p, uint32_t* __restrict__ err) {
+  constexpr uint32_t RUN = FIELDS * T;               // values of a record's run
+  constexpr uint32_t SLOT = T == 1 ? RUN : RUN + 2;  // padded against bank conflicts
+  __shared__ __align__(16) uint64_t stage[BLOCK * SLOT];
+  __shared__ mf_v4i af[MF_FRAGS * 64];
+  const uint32_t lane = threadIdx.x & 63u;
+  uint64_t* const slab = stage + (size_t)(threadIdx.x & ~63u) * SLOT;
+  uint4* const slab4 = reinterpret_cast<uint4*>(slab);
+  const uint32_t iw = __builtin_amdgcn_readfirstlane(blockIdx.x * BLOCK + (threadIdx.x & ~63u));
+  const uint32_t nrec = iw < n ? (n - iw < 64u ? n - iw : 64u) : 0u;  // records of this wave
+  uint4* const recs = reinterpret_cast<uint4*>(st + iw);
+
+#pragma unroll
+  for (uint32_t q = 0; q < 5; ++q)
+    if (64u * q + lane < 5u * nrec) slab4[64u * q + lane] = recs[64u * q + lane];
+  mf_stage_operands(af, mtabs, threadIdx.x, BLOCK);
+  __syncthreads();
+  uint32_t x[NW];
+  uint32_t pos = 0, sp = 0;
+  bool active = lane < nrec;
+  if (active) {
+    load_record(reinterpret_cast<const rlx_state*>(slab), lane, x, pos, sp);
+    const uint32_t bad = check_record(x, pos, sp, p);
+    if (bad) {
+      atomicOr(err, bad);
+      active = false;
+    }
+  }
+  const uint64_t act = __ballot(active);
+  if (act == 0) return;
+  if (!active) set_one(x);
+  // one position for all the wave's records?
+  const uint32_t pos0 = __builtin_amdgcn_readfirstlane(__shfl(pos, __ffsll((unsigned long long)act) - 1));
+  const bool same = __all(!active || pos == pos0);
+  const bool aligned16 = (reinterpret_cast<uintptr_t>(out) & 15) == 0;
+  const bool pairs = same && (pos0 & 1u) == 0 && (count & 1u) == 0 && aligned16;
+  uint64_t* const rows = out + (uint64_t)iw * count;
+  wave_sync();
+
+  for (uint32_t k = 0;; ++k) {
+    // opaque: what follows from the lane and its position is worked out again
+    // in each step rather than kept in registers
+    uint32_t v = lane, ps = pos;
+    asm volatile("" : "+v"(v), "+v"(ps));
+    const uint32_t nadv = (ps + count) / FIELDS;
+    const bool mine = ((act >> v) & 1u) != 0;
+    if (!__any(mine && k <= nadv)) break;
+    // value f of the step has index 12 k + f - pos
+    if (__any(mine && FIELDS * k < ps + count)) {
+      convert_to_lds<K>(x, slab + v * SLOT + FIELDS * (k % T), false);
+      // a run is stored when it is full or no step with values follows
+      if (k % T == T - 1 || !__any(mine && FIELDS * (k + 1) < ps + count)) {
+        const uint32_t k0 = k - k % T;
+        wave_sync();
+        if (__all(mine && ps + count <= RUN)) {
+          // the rows' values are all here: the wave's rows are one run of
+          // 512 count bytes on a 512-byte boundary of the output
+          const uint32_t magic = (uint32_t)(0x100000000ull / count) + 1u;  // i / count = i magic >> 32 for i < 64 count
+          for (uint32_t e0 = 0; e0 < 32u * count; e0 += 64u) {
+            // every lane takes part in the exchange of positions; the last
+            // round's upper half (odd counts) repeats the last pair
+            const uint32_t e = e0 + v < 32u * count ? e0 + v : 32u * count - 1u;
+            const uint32_t r0 = count == 1 ? 2u * e : __umulhi(2u * e, magic);
+            const uint32_t r1 = count == 1 ? 2u * e + 1u : __umulhi(2u * e + 1u, magic);
+            const uint32_t f0 = 2u * e - r0 * count, f1 = 2u * e + 1u - r1 * count;
+            const uint64_t a = slab[r0 * SLOT + f0 + (uint32_t)__builtin_amdgcn_ds_bpermute((int)(4u * r0), (int)ps)];
+            const uint64_t b = slab[r1 * SLOT + f1 + (uint32_t)__builtin_amdgcn_ds_bpermute((int)(4u * r1), (int)ps)];
+            if (aligned16) {
+              store_pair<true>(rows + 2u * e, make_ulonglong2(a, b));
+            } else {
+              rows[2u * e] = a;
+              rows[2u * e + 1u] = b;
+            }
+          }
+        } else if (pairs) {
+          const int32_t j0 = (int32_t)(FIELDS * k0) - (int32_t)pos0;
+#pragma unroll
+          for (uint32_t q = 0; q < RUN / 2; ++q) {
+            const uint32_t e = 64u * q + v, rec = e / (RUN / 2), f = e % (RUN / 2);
+            const uint32_t j = (uint32_t)(j0 + (int32_t)(2u * f));
+            if (j < count && ((act >> rec) & 1u) != 0)
+              store_pair<false>(rows + (rec * count + j), reinterpret_cast<const ulonglong2*>(slab)[rec * (SLOT / 2) + f]);
+          }
+        } else {
+#pragma unroll 4
+          for (uint32_t q = 0; q < RUN; ++q) {
+            const uint32_t e = 64u * q + v, rec = e / RUN, f = e % RUN;
+            const uint32_t j = FIELDS * k0 + f - (uint32_t)__builtin_amdgcn_ds_bpermute((int)(4u * rec), (int)ps);
+            if (j < count && ((act >> rec) & 1u) != 0) rows[rec * count + j] = slab[rec * SLOT + f];
+          }
+        }
+        wave_sync();
+      }
+    }
+    if (mine && k == nadv) {
+      if (same) {
+        store_record(reinterpret_cast<rlx_state*>(slab), v, x, (ps + count) % FIELDS, p);
+      } else {
+        store_record(st, iw + v, x, (ps + count) % FIELDS, p);
+      }
+    }
+    if (__any(mine && k < nadv)) {
+      mfma_step_split(x, MfFromArray{af, v}, false);
+    }
+  }
+  if (same) {
+    // the records were all written to LDS in the last iteration
+    wave_sync();
+#pragma unroll
+    for (uint32_t q = 0; q < 5; ++q) {
+      const uint32_t e = 64u * q + lane;
+      if (((act >> (e / 5u)) & 1u) != 0) recs[e] = slab4[e];
+    }
+  }
+}
+
 // k_generate for records of several levels (p = RLX_P_RECORD), G <= 64 lanes
 // per record, so a record's lanes share a wave and write it back in place.
 // A wave in which each half (lanes 0..31, 32..63) has live records of one
@@ -1202,6 +1340,14 @@ int generate_impl(rlx_state* states, uint64_t n, uint64_t count, void* out, uint
   const uint32_t lgs = lg < 6 ? lg : 6;
   const int writeback = lg <= 6;
   const bool mf = g_step_kind.load(std::memory_order_relaxed) == RLX_STEP_MFMA;
+  if (!TRACE && lgs == 0 && mf && !force_general && count <= ROWS_MAX_COUNT) {
+    if (count <= FIELDS) {
+      k_generate_rows<K, 1><<<grid, BLOCK, 0, s>>>(states, (uint32_t)n, (uint32_t)count, o, t.P, p, err);
+    } else {
+      k_generate_rows<K, 2><<<grid, BLOCK, 0, s>>>(states, (uint32_t)n, (uint32_t)count, o, t.P, p, err);
+    }
+    return launch_status();
+  }
 #define RLX_GEN(L)                                                                                    \
   case L:                                                                                             \
     if (mf) {                                                                                         \
