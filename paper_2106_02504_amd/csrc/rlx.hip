@@ -303,6 +303,7 @@ struct LevelSet {
   const uint32_t* C[MAX_RECORD_LEVELS];
   const uint32_t* M[MAX_RECORD_LEVELS];
   const uint32_t* W[MAX_RECORD_LEVELS];
+  const uint32_t* S[MAX_RECORD_LEVELS];
 };
 
 // Index of level p in L, or -1.
@@ -691,14 +692,18 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(T == 1 ? 
 
 // k_generate for records of several levels (p = RLX_P_RECORD), G <= 64 lanes
 // per record, so a record's lanes share a wave and write it back in place.
-// A wave in which each half (lanes 0..31, 32..63) has live records of one
-// level takes the matrix-core step with one multiplier per half (operands
-// read through the L1, as the batched kernel does for items of mixed
-// levels); with G >= 32 a half is one record, so this is every wave.  A wave
-// with mixed levels inside a half multiplies each lane by its own level's
-// A^G with the generic multiplication.
+// With 32 or 64 lanes a half-wave is one record: its lanes start together
+// from the record's digits and their level's start operands, and the
+// matrix-core step takes one multiplier per half (operands read through the
+// L1, as the batched kernel does for items of mixed levels).  With fewer
+// lanes a wave whose halves each hold one level steps the same way, and a
+// wave with mixed levels inside a half multiplies each lane by its own level's
+// A^G with the generic multiplication.  3 waves per SIMD but for 64 lanes:
+// with two multipliers in flight 4 waves spill (65 536 x 4096 in no order 488
+// us against 447; 8192 x 1000: 25.1 against 26.3, and 43.8 with the 8 lanes
+// taken before).
 template <Out K, int LGS>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(K == Out::NORMAL ? 3 : 4))) void k_generate_levels(
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(K == Out::NORMAL || LGS < 6 ? 3 : 4))) void k_generate_levels(
     rlx_state* __restrict__ st, uint32_t n, uint64_t count, uint64_t* __restrict__ out, LevelSet L, uint32_t lg,
     uint32_t* __restrict__ err) {
   constexpr bool STAGED = LGS > 0;
@@ -708,21 +713,29 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(K == Out:
   const uint32_t i = (uint32_t)(tid >> lg);
   const uint32_t l = (uint32_t)tid & ((1u << lg) - 1u);
 
+  constexpr bool SHARED = LGS >= 5;  // as in k_generate
   uint32_t x[NW];
-  uint32_t pos = 0, sp = 0;
+  uint32_t pos = 0, sp = 0, w = 0;
   int li = -1;
   bool active = (tid >> lg) < n;
+  if constexpr (SHARED) w = load_record_word(st, i, active, threadIdx.x & 31u, pos, sp);
   if (active) {
-    load_record(st, i, x, pos, sp);
+    uint32_t bad;
+    if constexpr (SHARED) {
+      bad = check_record_word(st, i, w, pos, sp, sp);
+    } else {
+      load_record(st, i, x, pos, sp);
+      bad = check_record(x, pos, sp, sp);
+    }
     li = level_index(L, sp);
-    const uint32_t bad = check_record(x, pos, sp, sp) | (li < 0 ? RLX_ERR_BAD_P : 0u);
+    if (li < 0) bad |= RLX_ERR_BAD_P;
     if (bad) {
       if (l == 0) atomicOr(err, bad);
       active = false;
     }
   }
   if (!active) {
-    set_one(x);
+    if constexpr (!SHARED) set_one(x);
     pos = 0;
     li = -1;
   }
@@ -730,6 +743,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(K == Out:
   // one multiplier per half: lanes 0..31 and 32..63 are its two state
   // tiles); a half with no live record takes the other half's
   const uint64_t act = __ballot(li >= 0);
+  if (act == 0) return;
   const uint64_t act0 = act & 0xFFFFFFFFull, act1 = act >> 32;
   const int first0 = act0 ? __ffsll((unsigned long long)act0) - 1 : (act1 ? 32 + __ffsll((unsigned long long)act1) - 1 : 0);
   const int first1 = act1 ? 32 + __ffsll((unsigned long long)act1) - 1 : first0;
@@ -737,7 +751,22 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(K == Out:
   const int u1 = __builtin_amdgcn_readfirstlane(__shfl(li, first1));
   const bool uniform = __all(li < 0 || li == ((threadIdx.x & 32) ? u1 : u0));
   const uint32_t nadv = (uint32_t)((pos + count) / FIELDS);
-  if (STAGED && active) skip_windows(x, l, level_ptr(L.W, li));
+  if constexpr (SHARED) {
+    mf_v4i b[6];
+    const mf_v4i* const s0 = reinterpret_cast<const mf_v4i*>(level_ptr(L.S, u0)) + (threadIdx.x & 63u);
+    const mf_v4i* const s1 = reinterpret_cast<const mf_v4i*>(level_ptr(L.S, u1)) + (threadIdx.x & 63u);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      b[k] = s0[64 * k];
+      b[3 + k] = s1[64 * (LGS == 6 ? 3 + k : k)];
+    }
+    uint8_t* const lds = reinterpret_cast<uint8_t*>(stage + (size_t)(threadIdx.x & ~63u) * SLOT_VALUES);
+    mf_shared_digits(w, lds, threadIdx.x & 63u);
+    mf_shared_product<LGS == 6>(lds, b, x, threadIdx.x & 63u);
+    wave_sync();
+  } else if (STAGED && active) {
+    skip_windows(x, l, level_ptr(L.W, li));
+  }
 
   for (uint32_t k = 0;; ++k) {
     const uint32_t t = l + (k << lg);
@@ -763,13 +792,13 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(K == Out:
       group_store<LGS>(stage, threadIdx.x, ls, jb, count, active, row);
     }
     if (__any(live && t + (1u << lg) <= nadv)) {
-      if (uniform && u0 == u1) {
+      if (LGS == 6 || (uniform && u0 == u1)) {
         // one level for the wave: one operand fetch serves both halves
         mfma_step_split(x, MfFromBuffer(level_ptr(L.M, u0) + (size_t)lg * MF_LEVEL_WORDS, threadIdx.x & 63), false);
-      } else if (uniform) {
+      } else if (SHARED || uniform) {
         mfma_step_split(x, MfFromBuffer(level_ptr(L.M, u0) + (size_t)lg * MF_LEVEL_WORDS, threadIdx.x & 63),
                         MfFromBuffer(level_ptr(L.M, u1) + (size_t)lg * MF_LEVEL_WORDS, threadIdx.x & 63), false);
-      } else if (active) {
+      } else if (!SHARED && active) {
         uint32_t a[NW];
         load_words(level_ptr(L.C, li) + (size_t)lg * FOLD_ROW_WORDS, a);  // C_0 = A^G
         mulmod_inplace(x, a);
@@ -1201,48 +1230,89 @@ namespace {
 std::atomic<uint32_t> g_lanes_override{0};
 std::atomic<int> g_step_kind{RLX_STEP_MFMA};
 
-// Lanes per record: the largest power of two G <= RLX_MAX_LANES such that
-// the launch stays within `target` lanes and every lane still takes at least
-// `min_steps` generator steps -- or, while the launch has fewer lanes than
-// one wave per SIMD (2^16), at least one step.  A lane pays one windowed
-// multiplication per non-zero 16-bit digit of its index at start-up, so G
-// trades start-up work against parallelism and against the length of the
-// contiguous runs each store instruction writes (16 G bytes per record).
-// With the matrix-core step (a cheaper step, so start-up weighs more, but
-// waves that each take half as long and leave a shorter tail) the limits
-// are 2^21 lanes and 8 steps, which picks G = 32 on the many-streams shape
-// (65 536 x 4096: 0.372 ms against 0.411 at G = 16 and 0.427 at G = 64);
-// with the vector-ALU step, 2^20 lanes and 16 steps, G = 16 there.  A single
-// stream of 2^20 values ran in 32 us at G = 65536 against 68 us at 4096.
-uint32_t auto_lanes(uint64_t n, uint64_t count, bool mf) {
+// Lanes per record with the vector-ALU step: the largest power of two G such
+// that the launch stays within 2^20 lanes and every lane still takes at least
+// 16 generator steps -- or, while the launch has fewer lanes than one wave per
+// SIMD (2^16), at least one step.
+uint32_t auto_lanes_valu(uint64_t n, uint64_t count) {
   const uint64_t steps = count / FIELDS + 1;
-  const uint64_t target = mf ? 1ull << 21 : 1ull << 20, sparse = 1ull << 16;
-  const uint64_t min_steps = mf ? 8 : 16;
   uint64_t g = 1;
   for (;;) {
     const uint64_t g2 = g * 2;
-    if (g2 > RLX_MAX_LANES || n > target / g2 || steps / g2 == 0) break;
-    if (steps / g2 < min_steps && n > sparse / g2) break;
+    if (g2 > RLX_MAX_LANES || n > (1ull << 20) / g2 || steps / g2 == 0) break;
+    if (steps / g2 < 16 && n > (1ull << 16) / g2) break;
     g = g2;
   }
   return (uint32_t)g;
 }
 
-uint32_t lanes_for(uint64_t n, uint64_t count) {
+// Lanes per record with the matrix-core step: the power of two G with the
+// smallest estimate (microseconds) of the launch's time, up to 2^21 lanes.
+//  * Computing: a lane takes ceil(blocks / G) steps after a start-up worth
+//    3.5 steps (2..16 lanes: a generic product) or 2.75 (32 and more: shared
+//    by a half-wave; 1: none), and a step takes 1.15 us of latency or 0.65 us
+//    per wave that its SIMD holds, whichever is longer.
+//  * Storing: rates by the length of the runs a group writes (16 G bytes an
+//    instruction), measured over buffers larger than the last-level cache:
+//    2.6 TB/s (one lane, rows of more than two steps; 4.2 for shorter ones,
+//    kept whole) up to 6 TB/s for 32 lanes and more.
+//  * The longer of the two plus a third of the shorter; more than 64 lanes
+//    need a second launch, 5 us.  Among those, estimates within 5% go to more
+//    lanes.
+// Against the best G in sweeps of 60 shapes (1 to 2^20 records, 16 to 2^22
+// values) this is 0.8% slower on average; the rule before (most lanes up to
+// 2^21 with at least 8 steps each) was 5.2%: 5000 x 1001 took 21.5 us with 8
+// lanes, 15.5 with 32; 65 536 x 250 50 us with 2 lanes, 40 with 8; 2^18 x 128
+// 106 us with 1, 90 with 2.
+// Normals take 2.1 times a step's work (16 384 x 1000: 55 us with 8 lanes, 60
+// with 16).  Records of several levels (Draw::LEVELS) count 2 below 32 lanes:
+// there a half-wave may mix levels, and its lanes then each run a generic
+// product a step, 4 steps' worth (30 000 x 1000 over five levels: 94 us with
+// 8 lanes and 64 with 32 in no order, 58 and 65 sorted by level).
+enum class Draw { UNIFORM, NORMAL, LEVELS };
+
+uint32_t auto_lanes_mfma(uint64_t n, uint64_t count, Draw kind) {
+  const double bytes = (double)n * (double)(count * 8 + sizeof(rlx_state) * 2) * 1e-6;  // at 1 TB/s: us
+  const uint64_t blocks = count / FIELDS + 1;
+  double best = 0;
+  uint64_t pick = 1;
+  for (uint64_t g = 1; g <= RLX_MAX_LANES && (g == 1 || (g <= 2 * blocks && n <= (1ull << 21) / g)); g *= 2) {
+    const double waves = (double)n * (double)g / 65536.0;
+    const double each = kind == Draw::NORMAL ? 2.1 : kind == Draw::LEVELS && g < 32 ? 2.0 : 1.0;
+    const double steps = each * (double)((blocks + g - 1) / g) + (g == 1 ? 0.0 : g < 32 ? 3.5 : 2.75);
+    const double compute = steps * (waves * 0.65 > 1.15 ? waves * 0.65 : 1.15) + (g > 64 ? 5.0 : 0.0);
+    const double rate = g == 1 ? (count <= 2 * FIELDS ? 4.2 : 2.6) : g == 2 ? 3.2 : g == 4 ? 3.8 : g == 8 ? 5.0
+                        : g == 16 ? 5.6 : 6.0;
+    const double store = bytes / rate;
+    const double t = compute > store ? compute + store / 3 : store + compute / 3;
+    if (g == 1 || t < best || (pick > 64 && t < 1.05 * best)) {
+      if (g == 1 || t < best) best = t;
+      pick = g;
+    }
+  }
+  return (uint32_t)pick;
+}
+
+uint32_t auto_lanes(uint64_t n, uint64_t count, bool mf, Draw kind) {
+  return mf ? auto_lanes_mfma(n, count, kind) : auto_lanes_valu(n, count);
+}
+
+uint32_t lanes_for(uint64_t n, uint64_t count, Draw kind = Draw::UNIFORM) {
   const uint32_t o = g_lanes_override.load(std::memory_order_relaxed);
-  return o ? o : auto_lanes(n, count, g_step_kind.load(std::memory_order_relaxed) == RLX_STEP_MFMA);
+  return o ? o : auto_lanes(n, count, g_step_kind.load(std::memory_order_relaxed) == RLX_STEP_MFMA, kind);
 }
 
 // Argument checks shared by the generate calls; on success *lg is log2 of
 // the lanes per record and *grid covers n << lg lanes.
 int generate_args(const rlx_state* states, uint64_t n, uint64_t count, const void* out, uint32_t p,
-                  uint32_t* lg, dim3* grid, bool record_levels = false) {
+                  uint32_t* lg, dim3* grid, Draw kind) {
+  const bool record_levels = kind == Draw::LEVELS;
   if (!states || !out) return RLX_EINVAL;
   if (record_levels ? p != RLX_P_RECORD : !valid_p(p)) return RLX_EINVAL;
   if (!aligned(states, 16) || !aligned(out, 8)) return RLX_EINVAL;
   if (n > RLX_MAX_STREAMS || count > RLX_MAX_COUNT) return RLX_EINVAL;
   if (count > UINT64_MAX / 8 / n) return RLX_EINVAL;
-  uint32_t G = lanes_for(n, count);
+  uint32_t G = lanes_for(n, count, kind);
   if (record_levels && G > 64) G = 64;  // a record's lanes in one wave
   *lg = (uint32_t)__builtin_ctz(G);
   if (n > (UINT64_MAX >> *lg)) return RLX_EINVAL;
@@ -1279,6 +1349,7 @@ int level_set(LevelSet* L) {
     L->C[L->n] = kv.second.C;
     L->M[L->n] = kv.second.P;
     L->W[L->n] = kv.second.W;
+    L->S[L->n] = kv.second.S;
     ++L->n;
   }
   return RLX_OK;
@@ -1289,7 +1360,7 @@ int generate_levels_impl(rlx_state* states, uint64_t n, uint64_t count, void* ou
   if (n == 0 || count == 0) return RLX_OK;
   uint32_t lg;
   dim3 grid;
-  int rc = generate_args(states, n, count, out, RLX_P_RECORD, &lg, &grid, true);
+  int rc = generate_args(states, n, count, out, RLX_P_RECORD, &lg, &grid, Draw::LEVELS);
   if (rc) return rc;
   hipStream_t s = as_stream(stream);
   LevelSet L;
@@ -1321,7 +1392,7 @@ int generate_impl(rlx_state* states, uint64_t n, uint64_t count, void* out, uint
   if (n == 0 || count == 0) return RLX_OK;
   uint32_t lg;
   dim3 grid;
-  int rc = generate_args(states, n, count, out, p, &lg, &grid);
+  int rc = generate_args(states, n, count, out, p, &lg, &grid, K == Out::NORMAL ? Draw::NORMAL : Draw::UNIFORM);
   if (rc) return rc;
   if (TRACE) {
     if (!trace || !aligned(trace, 8)) return RLX_EINVAL;
@@ -1369,7 +1440,7 @@ int generate_lcg52_impl(rlx_state* states, uint64_t n, uint64_t count, double* o
   if (n == 0 || count == 0) return RLX_OK;
   uint32_t lg;
   dim3 grid;
-  int rc = generate_args(states, n, count, out, p, &lg, &grid);
+  int rc = generate_args(states, n, count, out, p, &lg, &grid, Draw::UNIFORM);
   if (rc) return rc;
   hipStream_t s = as_stream(stream);
   Tables t;
