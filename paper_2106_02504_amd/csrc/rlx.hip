@@ -356,39 +356,6 @@ __global__ __launch_bounds__(BLOCK) void k_skip_levels(rlx_state* __restrict__ s
 // ---------------------------------------------------------------------------
 // generation (sections 2.1-2.3)
 
-// Word rr of record i (0 from word 18 on) and the record's position and
-// level, for a half-wave whose lanes share the record; without a record
-// (active false) the state 1.
-__device__ __forceinline__ uint32_t load_record_word(const rlx_state* __restrict__ st, uint64_t i, bool active,
-                                                     uint32_t rr, uint32_t& pos, uint32_t& p) {
-  uint32_t w = rr == 0 ? 1u : 0u;
-  if (active) {
-    const uint32_t* const r = reinterpret_cast<const uint32_t*>(st + i);
-    if (rr < NW) w = r[rr];
-    const uint2 v = *reinterpret_cast<const uint2*>(r + NW);
-    pos = v.x;
-    p = v.y;
-  }
-  return w;
-}
-
-// check_record for a half-wave that holds the record's words one per lane
-// (w): X >= m needs words 8..17 all ones, and only then is the record
-// compared with m.
-__device__ __forceinline__ uint32_t check_record_word(const rlx_state* __restrict__ st, uint64_t i, uint32_t w,
-                                                      uint32_t pos, uint32_t sp, uint32_t p) {
-  uint32_t bad = 0;
-  if (sp != p) bad |= RLX_ERR_BAD_P;
-  if (pos > 11) bad |= RLX_ERR_BAD_POS;
-  const uint64_t ones = __ballot(w == 0xFFFFFFFFu) >> (threadIdx.x & 32u);
-  if ((ones & 0x3FF00u) == 0x3FF00u) {
-    uint32_t x[NW], a, b;
-    load_record(st, i, x, a, b);
-    if (geq_m(x)) bad |= RLX_ERR_BAD_X;
-  }
-  return bad;
-}
-
 // X_l = A^l X_0 for lane l of records whose lanes fill half-waves (G >= 32),
 // X_0's word rr in lane rr of each half (mf_shared_product).  The factors A^l
 // are ready-made operands for l < 64; for larger G (one wave of a record's

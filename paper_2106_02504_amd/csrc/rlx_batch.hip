@@ -14,10 +14,9 @@
 // Segments are sorted by length (longest first) inside a level and items by
 // cost, and the hardware dispatches waves in item order, so late waves get
 // short items (longest-processing-time order); long requests are cut so
-// that no item dominates the launch.  One wave per item, rather than
-// persistent waves popping items from a counter, keeps the kernel's
-// registers low: with the vector step it ran at 5 waves per SIMD against 4
-// for the persistent form; with the matrix-core step it runs at 3.
+// that no item dominates the launch.  One wave per item (or a part of one,
+// share_log2), rather than persistent waves popping items from a counter,
+// keeps the kernel's registers low: 118 VGPRs and 4 waves per SIMD.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -75,51 +74,65 @@ struct Header {
   uint32_t p[MAX_LEVELS];
 };
 
+// A plan with few items leaves most of the chip idle while one wave runs the
+// longest of them (256 requests up to 65 536 values: 264 items, the longest 64
+// iterations of a wave, 99 us of it), so the grid is at least MIN_WAVES waves
+// and spare ones share the items: 2^share_log2 waves an item, each taking a
+// run of at least MIN_SHARE iterations of every segment.  The item count is
+// read on the device, so a captured launch shares out whatever an update left.
+// That plan's launch takes 12 us this way, with planning and upload 39 us
+// instead of 99; 424 requests up to 2^19 values 36 us instead of 92.  A plan
+// of 8192 requests up to 2^20 values (19 000 items) shares nothing.
+constexpr uint32_t MIN_WAVES = 8192, MAX_SHARE_LOG2 = 6, MIN_SHARE = 2;
+
+__device__ __forceinline__ uint32_t share_log2(uint32_t n_items, uint32_t waves) {
+  uint32_t ls = 0;
+  while (ls < MAX_SHARE_LOG2 && n_items <= (waves >> (ls + 1))) ++ls;
+  return ls;
+}
+
+// Blocks of a segment of `nblocks` that each of 2^ls waves takes, in whole
+// iterations of 2^lgs blocks.
+__device__ __forceinline__ uint32_t part_blocks(uint32_t nblocks, uint32_t lgs, uint32_t ls) {
+  const uint32_t its = (nblocks + (1u << lgs) - 1u) >> lgs;
+  const uint32_t per = (its + (1u << ls) - 1u) >> ls;
+  return (per > MIN_SHARE || ls == 0 ? per : MIN_SHARE) << lgs;
+}
+
 template <Out K, int LGS, bool MF>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MF ? 3 : 4))) void k_batch(const rlx_state* __restrict__ st,
                                                  const Segment* __restrict__ segs,
                                                  const Item* __restrict__ items, Header* __restrict__ hdr,
                                                  uint64_t* __restrict__ out, uint32_t* __restrict__ err) {
   constexpr uint32_t G = 1u << LGS;
-  constexpr uint32_t NO_SLOT = 0xFFFFFFFFu;
+  constexpr bool SHARED = MF && LGS >= 5;  // a segment's lanes fill half-waves
   __shared__ __align__(16) uint64_t stage[BLOCK * SLOT_VALUES];
   __shared__ mf_v4i af_lds[MF ? MF_FRAGS * 64 : 1];
-  __shared__ uint32_t wave_slot[BLOCK / WAVE];
   const uint32_t tid_blk = threadIdx.x;
   const uint32_t lane = tid_blk & (WAVE - 1);
   const uint32_t team = lane >> LGS;
   const uint32_t l = lane & (G - 1);
   const uint32_t n_items = __builtin_amdgcn_readfirstlane(hdr->n_items);
   {
-    // wave w of the grid runs item w; the grid covers the plan's capacity,
-    // so waves past the current item count exit at once (after the block's
-    // set-up below)
-    const uint32_t it = __builtin_amdgcn_readfirstlane(blockIdx.x * (BLOCK / WAVE) + tid_blk / WAVE);
-    // MF: when every item of the block has the same level (items are laid
-    // out level by level, so nearly always), the block stages that level's
-    // matrix-core operands for A^G in LDS once; otherwise each wave reads
-    // its own level's operands from the table at every step
-    bool lds_ok = false;
+    // waves (it << ls) .. + 2^ls - 1 of the grid share item `it`; the grid
+    // covers the plan's capacity, so waves past the current item count exit at
+    // once
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(blockIdx.x * (BLOCK / WAVE) + tid_blk / WAVE);
+    const uint32_t ls = share_log2(n_items, gridDim.x * (BLOCK / WAVE));
+    const uint32_t it = wave >> ls, part = wave & ((1u << ls) - 1u);
+    if (it >= n_items) return;  // the whole block: items come in groups of four
+    // MF: the block stages its level's matrix-core operands for A^G in LDS;
+    // its items (group_items) and the waves that share one have one level.
+    // (With mixed blocks, whose waves read their operands through the L1 and
+    // so had the loop a second time in the code, 8192 requests up to 2^14
+    // values took 47 us against 43, 3000 up to 2^18 123 us against 119, and
+    // the kernel 146 VGPRs against 118.)
+    const uint32_t slot = __builtin_amdgcn_readfirstlane(items[it].slot);
     if constexpr (MF) {
-      if (lane == 0) wave_slot[tid_blk / WAVE] = it < n_items ? items[it].slot : NO_SLOT;
-      __syncthreads();
-      uint32_t s0 = NO_SLOT;
-      bool same = true;
-#pragma unroll
-      for (uint32_t w = 0; w < BLOCK / WAVE; ++w) {
-        const uint32_t v = __builtin_amdgcn_readfirstlane(wave_slot[w]);
-        if (v != NO_SLOT) {
-          same = same && (s0 == NO_SLOT || v == s0);
-          s0 = s0 == NO_SLOT ? v : s0;
-        }
-      }
-      lds_ok = same && s0 != NO_SLOT;
-      if (lds_ok) mf_stage_operands(af_lds, hdr->M[s0] + (size_t)LGS * MF_LEVEL_WORDS, tid_blk, BLOCK);
+      mf_stage_operands(af_lds, hdr->M[slot] + (size_t)LGS * MF_LEVEL_WORDS, tid_blk, BLOCK);
       __syncthreads();
     }
-    if (it >= n_items) return;
     const Item item = items[it];
-    const uint32_t slot = __builtin_amdgcn_readfirstlane(item.slot);
     const uint32_t* __restrict__ ctabs = hdr->C[slot];
     const uint32_t* __restrict__ wtabs = hdr->W[slot];
     const uint32_t p = __builtin_amdgcn_readfirstlane(hdr->p[slot]);
@@ -128,23 +141,55 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MF ? 3 : 
     uint32_t nblocks = 0;
     uint32_t x[NW];
     uint64_t first = 0;  // this lane's first block: the segment's first + l
+    // this wave's part of every segment: blocks from..from + nblocks - 1
+    uint32_t from = 0;
+    uint32_t w = 0;
     if (active) {
       const Segment& sg = segs[si];
-      uint32_t pos, sp;
-      load_record(st, sg.state, x, pos, sp);
-      uint32_t bad = 0;
-      if (sp != p) bad |= RLX_ERR_BAD_P;
-      if (geq_m(x)) bad |= RLX_ERR_BAD_X;
-      if (bad) {
-        if (l == 0) atomicOr(err, bad);
-        active = false;
-      } else {
-        nblocks = sg.nblocks;
-        first = sg.block + l;
+      const uint32_t per = part_blocks(sg.nblocks, LGS, ls);
+      from = part * per;
+      nblocks = from < sg.nblocks ? (sg.nblocks - from < per ? sg.nblocks - from : per) : 0u;
+      active = nblocks != 0;
+      if (SHARED || active) {
+        // one half-wave is one segment if SHARED, so its lanes agree
+        uint32_t pos, sp;
+        uint32_t bad = 0;
+        if constexpr (SHARED) {
+          w = load_record_word(st, sg.state, true, tid_blk & 31u, pos, sp);
+          bad = check_record_word(st, sg.state, w, 0u, sp, p);
+        } else {
+          load_record(st, sg.state, x, pos, sp);
+          if (sp != p) bad |= RLX_ERR_BAD_P;
+          if (geq_m(x)) bad |= RLX_ERR_BAD_X;
+        }
+        if (bad) {
+          if (l == 0) atomicOr(err, bad);
+          active = false;
+        }
+        first = sg.block + from + l;
       }
     }
-    if (!active) set_one(x);
-    skip_windows(x, first, wtabs);
+    if (!__any(active)) return;
+    if constexpr (SHARED) {
+      // X_l = A^first X_0: the lowest 16-bit digit of `first` by the shared
+      // product, the rest (segments that start past 65 536 steps) by windows
+      uint32_t y[NW];
+      mf_v4i b[6];
+      if (!active) first = 0;
+      load_words(wtabs + (size_t)(first & (WIN_COLS - 1u)) * NW, y);
+      mf_shared_operands(y, b);
+      uint8_t* const lds = reinterpret_cast<uint8_t*>(stage + (size_t)(tid_blk - lane) * SLOT_VALUES);
+      mf_shared_digits(w, lds, lane);
+      mf_shared_product<LGS == 6>(lds, b, x, lane);
+      wave_sync();
+      skip_windows(x, first & ~(uint64_t)(WIN_COLS - 1u), wtabs);
+    } else {
+      if (!active) {
+        set_one(x);
+        first = 0;
+      }
+      skip_windows(x, first, wtabs);
+    }
     const uint32_t* __restrict__ ctab = ctabs + (size_t)LGS * FOLD_ROW_WORDS;
     // Output window of the segment: base[u] for u < span, with the
     // segment's first field at u = rel (rel >= -11; span < 2^30 because
@@ -157,39 +202,28 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MF ? 3 : 
     int32_t rel = 0;
     if (active) {
       const Segment& sg = segs[si];
-      const int64_t lo = sg.lo > sg.jbase ? sg.lo : sg.jbase;
-      const int64_t end = sg.jbase + (int64_t)FIELDS * nblocks;
+      const int64_t jbase = sg.jbase + (int64_t)FIELDS * from;
+      const int64_t lo = sg.lo > jbase ? sg.lo : jbase;
+      const int64_t end = jbase + (int64_t)FIELDS * nblocks;
       const int64_t hi = sg.hi < end ? sg.hi : end;
       base = out + lo;
       span = hi > lo ? (uint32_t)(hi - lo) : 0u;
-      rel = (int32_t)(sg.jbase - lo);
+      rel = (int32_t)(jbase - lo);
     }
-    // the loop, once per way of fetching the step's operands
-    auto run = [&](const auto& fetch) {
-      for (uint32_t k = 0;; ++k) {
-        const uint32_t t = l + (k << LGS);
-        const bool live = active && t < nblocks;
-        if (!__any(live)) break;
-        convert_to_lds<K>(x, stage + (size_t)tid_blk * SLOT_VALUES, false);
-        const int32_t u0 = rel + (int32_t)(FIELDS * (t - l));
-        group_store<LGS>(stage, tid_blk, l, u0, span, active, base);
-        if (__any(live && t + G < nblocks)) {
-          if constexpr (MF) {
-            mfma_step_split(x, fetch, false);
-          } else {
-            step(x, constant_table(ctab), false, SgprBarrier());
-          }
+    for (uint32_t k = 0;; ++k) {
+      const uint32_t t = l + (k << LGS);
+      const bool live = active && t < nblocks;
+      if (!__any(live)) break;
+      convert_to_lds<K>(x, stage + (size_t)tid_blk * SLOT_VALUES, false);
+      const int32_t u0 = rel + (int32_t)(FIELDS * (t - l));
+      group_store<LGS>(stage, tid_blk, l, u0, span, active, base);
+      if (__any(live && t + G < nblocks)) {
+        if constexpr (MF) {
+          mfma_step_split(x, MfFromArray{af_lds, lane}, false);
+        } else {
+          step(x, constant_table(ctab), false, SgprBarrier());
         }
       }
-    };
-    if constexpr (MF) {
-      if (lds_ok) {
-        run(MfFromArray{af_lds, lane});
-      } else {
-        run(MfFromBuffer(hdr->M[slot] + (size_t)LGS * MF_LEVEL_WORDS, lane));
-      }
-    } else {
-      run(0);
     }
   }
 }
@@ -203,7 +237,7 @@ struct rlx_plan {
   int device = 0;
   uint32_t lanes = 0, lg = 0;
   uint64_t seg_blocks = 0;
-  uint64_t cap = 0;  // segments (and items) the device buffers hold
+  uint64_t cap = 0;  // segments (and items, with MAX_EMPTY more) the device buffers hold
   Segment* d_segs = nullptr;
   Item* d_items = nullptr;
   Header* d_hdr = nullptr;
@@ -313,11 +347,41 @@ int plan_requests(const rlx_request* reqs, uint64_t n, uint32_t lg, uint64_t seg
   return RLX_OK;
 }
 
+// The items of a plan in launch order, regrouped so that the four items of a
+// block have one level and its operands are staged once: the items that start
+// with a full segment (level by level already) and the rest (by decreasing
+// cost over all levels) each keep their order within a level; a level's items
+// are taken when four have come up, and those left at the end of each part
+// with empty items to make four.  Returns the items written: a multiple of
+// four, at most items.size() + MAX_EMPTY.
+constexpr size_t GROUP = BLOCK / WAVE;
+constexpr size_t MAX_EMPTY = 2 * (GROUP - 1) * MAX_LEVELS;
+
+size_t group_items(const std::vector<Item>& items, uint32_t full_cost, Item* out) {
+  size_t n = 0, k = 0;
+  for (int part = 0; part < 2; ++part) {
+    Item held[MAX_LEVELS][GROUP];
+    size_t have[MAX_LEVELS] = {};
+    for (; k < items.size() && (part == 1 || items[k].cost == full_cost); ++k) {
+      const uint32_t s = items[k].slot;
+      held[s][have[s]++] = items[k];
+      if (have[s] == GROUP) {
+        for (const Item& it : held[s]) out[n++] = it;
+        have[s] = 0;
+      }
+    }
+    for (uint32_t s = 0; s < (uint32_t)MAX_LEVELS; ++s) {
+      if (have[s] == 0) continue;
+      for (size_t q = 0; q < GROUP; ++q) out[n++] = q < have[s] ? held[s][q] : Item{0, 0, s, 0};
+    }
+  }
+  return n;
+}
+
 int upload(rlx_plan* plan, const Planned& pl, hipStream_t s) {
   if (pl.segs.size() > plan->cap || pl.items.size() > plan->cap) return RLX_EINVAL;
   if (pl.ps.size() > MAX_LEVELS) return RLX_EINVAL;
   Header hd{};
-  hd.n_items = (uint32_t)pl.items.size();
   for (size_t k = 0; k < pl.ps.size(); ++k) {
     Tables t;
     const int rc = tables(pl.ps[k], s, &t);
@@ -329,17 +393,18 @@ int upload(rlx_plan* plan, const Planned& pl, hipStream_t s) {
   }
   // the previous upload must have left the staging buffers
   if (hipEventSynchronize(plan->uploaded) != hipSuccess) return RLX_EHIP;
+  const size_t n_items = group_items(pl.items, (uint32_t)plan->seg_blocks, plan->h_items);
+  hd.n_items = (uint32_t)n_items;
   *plan->h_hdr = hd;
   if (hipMemcpyAsync(plan->d_hdr, plan->h_hdr, sizeof(Header), hipMemcpyHostToDevice, s) != hipSuccess)
     return RLX_EHIP;
   if (!pl.segs.empty()) std::memcpy(plan->h_segs, pl.segs.data(), pl.segs.size() * sizeof(Segment));
-  if (!pl.items.empty()) std::memcpy(plan->h_items, pl.items.data(), pl.items.size() * sizeof(Item));
   if (!pl.segs.empty() &&
       hipMemcpyAsync(plan->d_segs, plan->h_segs, pl.segs.size() * sizeof(Segment), hipMemcpyHostToDevice, s) !=
           hipSuccess)
     return RLX_EHIP;
   if (!pl.items.empty() &&
-      hipMemcpyAsync(plan->d_items, plan->h_items, pl.items.size() * sizeof(Item), hipMemcpyHostToDevice, s) !=
+      hipMemcpyAsync(plan->d_items, plan->h_items, n_items * sizeof(Item), hipMemcpyHostToDevice, s) !=
           hipSuccess)
     return RLX_EHIP;
   if (hipEventRecord(plan->uploaded, s) != hipSuccess) return RLX_EHIP;
@@ -377,9 +442,12 @@ int plan_launch(rlx_plan* plan, const rlx_state* states, void* out, void* stream
   int rc = error_word(s, &err);
   if (rc) return rc;
   // One wave per item of a full plan (items never outnumber the segment
-  // capacity).  The grid depends only on the capacity, so a captured launch
-  // stays valid after updates; waves past the current item count exit.
-  const uint64_t blocks = (plan->cap + (BLOCK / WAVE) - 1) / (BLOCK / WAVE);
+  // capacity, plus the empty ones), and for small plans more (share_log2).  The grid depends only
+  // on the capacity, so a captured launch stays valid after updates; waves
+  // past the current item count exit.
+  const uint64_t waves =
+      std::max<uint64_t>(plan->cap + MAX_EMPTY, std::min<uint64_t>(MIN_WAVES, plan->cap << MAX_SHARE_LOG2));
+  const uint64_t blocks = (waves + (BLOCK / WAVE) - 1) / (BLOCK / WAVE);
   if (blocks == 0 || blocks > 0x7FFFFFFFull) return RLX_EINVAL;
   uint64_t* o = reinterpret_cast<uint64_t*>(out);
   const bool mf = rlx_step_kernel() == RLX_STEP_MFMA;
@@ -429,11 +497,11 @@ int rlx_plan_create(rlx_plan** plan, const rlx_request* reqs, uint64_t n, uint32
   p->seg_blocks = seg_blocks;
   p->cap = std::max<uint64_t>({capacity_segments, (uint64_t)pl.segs.size(), 1});
   if (hipMalloc(&p->d_segs, p->cap * sizeof(Segment)) != hipSuccess ||
-      hipMalloc(&p->d_items, p->cap * sizeof(Item)) != hipSuccess ||
+      hipMalloc(&p->d_items, (p->cap + MAX_EMPTY) * sizeof(Item)) != hipSuccess ||
       hipMalloc(&p->d_hdr, sizeof(Header)) != hipSuccess ||
       hipHostMalloc(&p->h_hdr, sizeof(Header), 0) != hipSuccess ||
       hipHostMalloc(&p->h_segs, p->cap * sizeof(Segment), 0) != hipSuccess ||
-      hipHostMalloc(&p->h_items, p->cap * sizeof(Item), 0) != hipSuccess) {
+      hipHostMalloc(&p->h_items, (p->cap + MAX_EMPTY) * sizeof(Item), 0) != hipSuccess) {
     free_plan(p);
     return RLX_ENOMEM;
   }
