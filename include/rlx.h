@@ -232,8 +232,8 @@ int rlx_skip(rlx_state *states, uint64_t n, const uint64_t *steps,
 
 /* Uniform doubles (section 2.3).  For every record i (luxury level p), draw
  * `count` values into out[i * count + j], j < count, and advance the record.
- * When the lanes of one record span several waves (rlx_lanes_per_stream
- * above 64), the record is advanced by a second launch on `stream` after the
+ * When the lanes of one record span several waves (more than 64 lanes per
+ * record), the record is advanced by a second launch on `stream` after the
  * draws, as rlx_skip_values would, so no lane can read a record that another
  * has already advanced; this holds for every generate entry point below.
  * A value is a 48-bit field v of the step's RANLUX numbers, converted as
@@ -331,11 +331,14 @@ int rlx_import_ranlux(rlx_state *states, uint64_t n, const uint64_t *packed,
  * record interleave its generator steps (lane l takes steps l, l + G, ...,
  * advancing by the launch-uniform multiplier A_p^G), and their values are
  * staged through LDS so that stores write contiguous runs of the output row.
- * By default G is picked from n and count (rlx_lanes_per_stream reports the
- * pick); rlx_set_lanes_per_stream(G) forces a power of two G <=
- * RLX_MAX_LANES for all
- * later calls in the process (0 restores the automatic pick).  The values
- * produced never depend on G. */
+ * By default a call picks G from n, count and the kind of draw, by an estimate
+ * of its time; rlx_lanes_per_stream reports the nominal number, the most
+ * lanes up to 2^21 in all that leave each at least 8 steps (2^20 and 16 with
+ * the vector-ALU step; one step while there are fewer than 2^16 lanes), from
+ * which a call's own pick may differ.  rlx_set_lanes_per_stream(G) forces a
+ * power of two G <= RLX_MAX_LANES for all later calls in the process, and is
+ * then what rlx_lanes_per_stream reports (0 restores the automatic pick).
+ * The values produced never depend on G. */
 int rlx_set_lanes_per_stream(uint32_t lanes);
 uint32_t rlx_lanes_per_stream(uint64_t n, uint64_t count);
 

@@ -376,7 +376,8 @@ def set_lanes_per_stream(lanes: int) -> None:
 
 
 def lanes_per_stream(n: int, count: int) -> int:
-    """The G a generate call with n records and `count` values would use."""
+    """The nominal number of lanes per record for n records and `count` values
+    (the forced one, if any); a generate call's own pick may differ."""
     return int(lib().rlx_lanes_per_stream(n, count))
 
 

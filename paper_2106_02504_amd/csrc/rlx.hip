@@ -1197,23 +1197,29 @@ namespace {
 std::atomic<uint32_t> g_lanes_override{0};
 std::atomic<int> g_step_kind{RLX_STEP_MFMA};
 
-// Lanes per record with the vector-ALU step: the largest power of two G such
-// that the launch stays within 2^20 lanes and every lane still takes at least
-// 16 generator steps -- or, while the launch has fewer lanes than one wave per
-// SIMD (2^16), at least one step.
-uint32_t auto_lanes_valu(uint64_t n, uint64_t count) {
+// Nominal lanes per record (rlx_lanes_per_stream), and those that generate
+// calls with the vector-ALU step take: the largest power of two G <=
+// RLX_MAX_LANES such that the launch stays within `target` lanes and every
+// lane still takes at least `min_steps` generator steps -- or, while the
+// launch has fewer lanes than one wave per SIMD (2^16), at least one step.
+// 2^21 lanes and 8 steps with the matrix-core step, 2^20 and 16 with the
+// vector-ALU step.
+uint32_t nominal_lanes(uint64_t n, uint64_t count, bool mf) {
   const uint64_t steps = count / FIELDS + 1;
+  const uint64_t target = mf ? 1ull << 21 : 1ull << 20, sparse = 1ull << 16;
+  const uint64_t min_steps = mf ? 8 : 16;
   uint64_t g = 1;
   for (;;) {
     const uint64_t g2 = g * 2;
-    if (g2 > RLX_MAX_LANES || n > (1ull << 20) / g2 || steps / g2 == 0) break;
-    if (steps / g2 < 16 && n > (1ull << 16) / g2) break;
+    if (g2 > RLX_MAX_LANES || n > target / g2 || steps / g2 == 0) break;
+    if (steps / g2 < min_steps && n > sparse / g2) break;
     g = g2;
   }
   return (uint32_t)g;
 }
 
-// Lanes per record with the matrix-core step: the power of two G with the
+// Lanes per record that generate calls with the matrix-core step take: the
+// power of two G with the
 // smallest estimate (microseconds) of the launch's time, up to 2^21 lanes.
 //  * Computing: a lane takes ceil(blocks / G) steps after a start-up worth
 //    3.5 steps (2..16 lanes: a generic product) or 2.75 (32 and more: shared
@@ -1227,8 +1233,7 @@ uint32_t auto_lanes_valu(uint64_t n, uint64_t count) {
 //    need a second launch, 5 us.  Among those, estimates within 5% go to more
 //    lanes.
 // Against the best G in sweeps of 60 shapes (1 to 2^20 records, 16 to 2^22
-// values) this is 0.8% slower on average; the rule before (most lanes up to
-// 2^21 with at least 8 steps each) was 5.2%: 5000 x 1001 took 21.5 us with 8
+// values) this is 0.8% slower on average; the nominal number is 5.2%: 5000 x 1001 took 21.5 us with 8
 // lanes, 15.5 with 32; 65 536 x 250 50 us with 2 lanes, 40 with 8; 2^18 x 128
 // 106 us with 1, 90 with 2.
 // Normals take 2.1 times a step's work (16 384 x 1000: 55 us with 8 lanes, 60
@@ -1260,13 +1265,11 @@ uint32_t auto_lanes_mfma(uint64_t n, uint64_t count, Draw kind) {
   return (uint32_t)pick;
 }
 
-uint32_t auto_lanes(uint64_t n, uint64_t count, bool mf, Draw kind) {
-  return mf ? auto_lanes_mfma(n, count, kind) : auto_lanes_valu(n, count);
-}
-
-uint32_t lanes_for(uint64_t n, uint64_t count, Draw kind = Draw::UNIFORM) {
+uint32_t lanes_for(uint64_t n, uint64_t count, Draw kind) {
   const uint32_t o = g_lanes_override.load(std::memory_order_relaxed);
-  return o ? o : auto_lanes(n, count, g_step_kind.load(std::memory_order_relaxed) == RLX_STEP_MFMA, kind);
+  if (o) return o;
+  return g_step_kind.load(std::memory_order_relaxed) == RLX_STEP_MFMA ? auto_lanes_mfma(n, count, kind)
+                                                                       : nominal_lanes(n, count, false);
 }
 
 // Argument checks shared by the generate calls; on success *lg is log2 of
@@ -1648,7 +1651,10 @@ int rlx_set_lanes_per_stream(uint32_t lanes) {
   return RLX_OK;
 }
 
-uint32_t rlx_lanes_per_stream(uint64_t n, uint64_t count) { return lanes_for(n, count); }
+uint32_t rlx_lanes_per_stream(uint64_t n, uint64_t count) {
+  const uint32_t o = g_lanes_override.load(std::memory_order_relaxed);
+  return o ? o : nominal_lanes(n, count, g_step_kind.load(std::memory_order_relaxed) == RLX_STEP_MFMA);
+}
 
 int rlx_set_step_kernel(int kind) {
   if (kind != RLX_STEP_MFMA && kind != RLX_STEP_VALU) return RLX_EINVAL;
