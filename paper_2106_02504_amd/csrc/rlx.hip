@@ -210,15 +210,43 @@ __global__ __launch_bounds__(64) void k_tab_start(const uint32_t* __restrict__ W
 // ---------------------------------------------------------------------------
 // seeding and skipping (section 2.4)
 
+// A wave's 64 records between memory and a slab of its own in LDS, as one run
+// of 5120 bytes: each instruction moves 1024 consecutive bytes where one lane
+// per record touches 40 lines with each of five.  Records iw .. iw + nrec - 1.
+constexpr uint32_t RECORD_QUADS = sizeof(rlx_state) / sizeof(uint4);
+
+__device__ __forceinline__ void load_slab(uint4* __restrict__ slab, const rlx_state* __restrict__ st, uint64_t iw,
+                                          uint32_t nrec, uint32_t lane) {
+  const uint4* const r = reinterpret_cast<const uint4*>(st + iw);
+#pragma unroll
+  for (uint32_t q = 0; q < RECORD_QUADS; ++q)
+    if (64u * q + lane < RECORD_QUADS * nrec) slab[64u * q + lane] = r[64u * q + lane];
+  wave_sync();
+}
+
+__device__ __forceinline__ void store_slab(rlx_state* __restrict__ st, const uint4* __restrict__ slab, uint64_t iw,
+                                           uint64_t act, uint32_t lane) {
+  uint4* const r = reinterpret_cast<uint4*>(st + iw);
+  wave_sync();
+#pragma unroll
+  for (uint32_t q = 0; q < RECORD_QUADS; ++q) {
+    const uint32_t e = 64u * q + lane;
+    if ((act >> (e / RECORD_QUADS)) & 1u) r[e] = slab[e];
+  }
+}
+
 // X = A_p^(2^96 id) from 1: the product of the seed windows of the non-zero
 // 16-bit digits of id (the first one copied, not multiplied: ids < 2^16 are
 // a table copy).
 __global__ __launch_bounds__(BLOCK) void k_init(rlx_state* __restrict__ st, uint64_t n,
                                                 const uint64_t* __restrict__ ids, uint64_t id0,
                                                 uint32_t p, const uint32_t* __restrict__ W) {
-  const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const uint64_t id = ids ? ids[i] : id0 + i;
+  __shared__ __align__(16) rlx_state slabs[BLOCK];
+  const uint32_t lane = threadIdx.x & 63u;
+  const uint64_t iw = (uint64_t)blockIdx.x * BLOCK + (threadIdx.x & ~63u);
+  const uint64_t i = iw + lane;
+  const bool live = i < n;
+  const uint64_t id = !live ? 0 : ids ? ids[i] : id0 + i;
   uint32_t x[NW];
   set_one(x);
   bool first = true;
@@ -235,7 +263,9 @@ __global__ __launch_bounds__(BLOCK) void k_init(rlx_state* __restrict__ st, uint
       mulmod_inplace(x, y);
     }
   }
-  store_record(st, i, x, 0u, p);
+  rlx_state* const slab = slabs + (threadIdx.x & ~63u);
+  store_record(slab, lane, x, 0u, p);
+  store_slab(st, reinterpret_cast<const uint4*>(slab), iw, __ballot(live), lane);
 }
 
 // Record of the block that this thread skips when every record has its own
