@@ -413,6 +413,11 @@ int rlx_plan_update(rlx_plan *plan, const rlx_request *reqs, uint64_t n, void *s
 int rlx_plan_info(const rlx_plan *plan, uint64_t *segments, uint64_t *items,
                   uint64_t *total_values);
 
+/* What the plan's current requests need: `extent` output elements (the
+ * largest out_offset + count) and `records` records (the largest state + 1),
+ * over requests with count > 0; 0 without any. */
+int rlx_plan_needs(const rlx_plan *plan, uint64_t *extent, uint64_t *records);
+
 /* Run the plan: one kernel on `stream`, one wave per work item (no
  * allocation, no synchronisation, no memset: capturable).
  * The launch reads the work list, its length and the luxury tables from the

@@ -67,6 +67,7 @@ _SIGS = {
     "rlx_constants": (None, [ctypes.POINTER(_u32), ctypes.POINTER(_u32)]),
     "rlx_plan_create": (_int, [ctypes.POINTER(_vp), _vp, _u64, _u32, _u64, _u64, _vp]),
     "rlx_plan_update": (_int, [_vp, _vp, _u64, _vp]),
+    "rlx_plan_needs": (_int, [_vp, ctypes.POINTER(_u64), ctypes.POINTER(_u64)]),
     "rlx_plan_info": (_int, [_vp, ctypes.POINTER(_u64), ctypes.POINTER(_u64), ctypes.POINTER(_u64)]),
     "rlx_plan_generate_f64": (_int, [_vp, _vp, _vp, _vp]),
     "rlx_plan_generate_u64": (_int, [_vp, _vp, _vp, _vp]),
@@ -124,6 +125,25 @@ def _stream(device: torch.device | None = None) -> int:
     return torch.cuda.current_stream(device).cuda_stream
 
 
+def _call(device: torch.device, name: str, *args) -> None:
+    """The library call `name` with `device` current and its current stream as
+    the last argument.  The device is switched only when another one is
+    current, and the stream's handle taken without wrapping it: the two
+    context managers and the Stream object cost about 3 us of a 10 us call."""
+    index, current = device.index, torch.cuda.current_device()
+    if index is None or index == current:
+        code = getattr(lib(), name)(*args, _raw_stream(current))
+    else:
+        with torch.cuda.device(index):
+            code = getattr(lib(), name)(*args, _raw_stream(index))
+    if code != 0:
+        raise RlxError(code, name)
+
+
+def _raw_stream(index: int) -> int:
+    return torch._C._cuda_getCurrentRawStream(index)
+
+
 def _ptr(t: torch.Tensor | None) -> int | None:
     return None if t is None else t.data_ptr()
 
@@ -159,8 +179,7 @@ def init_streams(states: torch.Tensor, p: int, ids: torch.Tensor | None = None, 
     n = _need_states(states)
     if ids is not None:
         _need_u64_vector(ids, n, "ids")
-    with torch.cuda.device(states.device):
-        _check(lib().rlx_init_streams(states.data_ptr(), n, _ptr(ids), id0, p, _stream()), "rlx_init_streams")
+    _call(states.device, "rlx_init_streams", states.data_ptr(), n, _ptr(ids), id0, p)
     return states
 
 
@@ -174,8 +193,7 @@ def skip(states: torch.Tensor, steps, p: int) -> torch.Tensor:
         ptr, s0 = steps.data_ptr(), 0
     else:
         ptr, s0 = None, int(steps)
-    with torch.cuda.device(states.device):
-        _check(lib().rlx_skip(states.data_ptr(), n, ptr, s0, p, _stream()), "rlx_skip")
+    _call(states.device, "rlx_skip", states.data_ptr(), n, ptr, s0, p)
     return states
 
 
@@ -188,8 +206,7 @@ def skip_values(states: torch.Tensor, values, p: int) -> torch.Tensor:
         ptr, v0 = values.data_ptr(), 0
     else:
         ptr, v0 = None, int(values)
-    with torch.cuda.device(states.device):
-        _check(lib().rlx_skip_values(states.data_ptr(), n, ptr, v0, p, _stream()), "rlx_skip_values")
+    _call(states.device, "rlx_skip_values", states.data_ptr(), n, ptr, v0, p)
     return states
 
 
@@ -200,9 +217,7 @@ def export_ranlux(states: torch.Tensor):
     packed = torch.zeros((n, 9), dtype=torch.int64, device=states.device)
     carry = torch.zeros((n,), dtype=torch.int32, device=states.device)
     pos = torch.zeros((n,), dtype=torch.int32, device=states.device)
-    with torch.cuda.device(states.device):
-        _check(lib().rlx_export_ranlux(states.data_ptr(), n, packed.data_ptr(), carry.data_ptr(), pos.data_ptr(),
-                                       _stream()), "rlx_export_ranlux")
+    _call(states.device, "rlx_export_ranlux", states.data_ptr(), n, packed.data_ptr(), carry.data_ptr(), pos.data_ptr())
     return packed, carry, pos
 
 
@@ -221,9 +236,7 @@ def import_ranlux(states: torch.Tensor, packed: torch.Tensor, carry: torch.Tenso
     need(carry, (n,), (torch.int32, torch.uint32), "carry")
     if pos is not None:
         need(pos, (n,), (torch.int32, torch.uint32), "pos")
-    with torch.cuda.device(states.device):
-        _check(lib().rlx_import_ranlux(states.data_ptr(), n, packed.data_ptr(), carry.data_ptr(), _ptr(pos), p,
-                                       _stream()), "rlx_import_ranlux")
+    _call(states.device, "rlx_import_ranlux", states.data_ptr(), n, packed.data_ptr(), carry.data_ptr(), _ptr(pos), p)
     return states
 
 
@@ -243,8 +256,7 @@ def generate_f64(states: torch.Tensor, count: int, p: int, out: torch.Tensor | N
     generate_normal_f64."""
     n = _need_states(states)
     out = _out(states, count, torch.float64, out)
-    with torch.cuda.device(states.device):
-        _check(lib().rlx_generate_f64(states.data_ptr(), n, count, out.data_ptr(), p, _stream()), "rlx_generate_f64")
+    _call(states.device, "rlx_generate_f64", states.data_ptr(), n, count, out.data_ptr(), p)
     return out
 
 
@@ -252,8 +264,7 @@ def generate_u64(states: torch.Tensor, count: int, p: int, out: torch.Tensor | N
     """The same draws as 48-bit integers (int64 tensor, values < 2^48)."""
     n = _need_states(states)
     out = _out(states, count, torch.int64, out)
-    with torch.cuda.device(states.device):
-        _check(lib().rlx_generate_u64(states.data_ptr(), n, count, out.data_ptr(), p, _stream()), "rlx_generate_u64")
+    _call(states.device, "rlx_generate_u64", states.data_ptr(), n, count, out.data_ptr(), p)
     return out
 
 
@@ -262,9 +273,7 @@ def generate_normal_f64(states: torch.Tensor, count: int, p: int, out: torch.Ten
     on the field pair of each position's step (include/rlx_gauss.hpp)."""
     n = _need_states(states)
     out = _out(states, count, torch.float64, out)
-    with torch.cuda.device(states.device):
-        _check(lib().rlx_generate_normal_f64(states.data_ptr(), n, count, out.data_ptr(), p, _stream()),
-               "rlx_generate_normal_f64")
+    _call(states.device, "rlx_generate_normal_f64", states.data_ptr(), n, count, out.data_ptr(), p)
     return out
 
 
@@ -274,8 +283,7 @@ def generate_f32(states: torch.Tensor, count: int, p: int, out: torch.Tensor | N
     record by count / 2 positions."""
     n = _need_states(states)
     out = _out(states, count, torch.float32, out)
-    with torch.cuda.device(states.device):
-        _check(lib().rlx_generate_f32(states.data_ptr(), n, count, out.data_ptr(), p, _stream()), "rlx_generate_f32")
+    _call(states.device, "rlx_generate_f32", states.data_ptr(), n, count, out.data_ptr(), p)
     return out
 
 
@@ -285,9 +293,7 @@ def generate_f64_lcg52(states: torch.Tensor, count: int, p: int, out: torch.Tens
     positions count these values."""
     n = _need_states(states)
     out = _out(states, count, torch.float64, out)
-    with torch.cuda.device(states.device):
-        _check(lib().rlx_generate_f64_lcg52(states.data_ptr(), n, count, out.data_ptr(), p, _stream()),
-               "rlx_generate_f64_lcg52")
+    _call(states.device, "rlx_generate_f64_lcg52", states.data_ptr(), n, count, out.data_ptr(), p)
     return out
 
 
@@ -339,9 +345,7 @@ def test_engine(states: torch.Tensor, count: int, p: int, mode: str) -> torch.Te
     m = ENGINE_MODES[mode]
     shape = (n,) if mode == "sum" else (n, count)
     out = torch.empty(shape, dtype=torch.float64, device=states.device)
-    with torch.cuda.device(states.device):
-        _check(lib().rlx_test_engine(states.data_ptr(), n, count, out.data_ptr(), m, p, _stream()),
-               "rlx_test_engine")
+    _call(states.device, "rlx_test_engine", states.data_ptr(), n, count, out.data_ptr(), m, p)
     if mode == "u48":
         return out.view(torch.int64)
     if mode == "f32":
@@ -363,9 +367,8 @@ def generate_f64_trace(states: torch.Tensor, count: int, p: int, out: torch.Tens
     elif (trace.dtype != torch.int64 or tuple(trace.shape) != (n, steps, 9) or not trace.is_contiguous()
           or trace.device != states.device):
         raise ValueError(f"trace must be a contiguous int64 tensor of shape {(n, steps, 9)} on {states.device}")
-    with torch.cuda.device(states.device):
-        _check(lib().rlx_generate_f64_trace(states.data_ptr(), n, count, out.data_ptr(), trace.data_ptr(),
-                                            steps, p, _stream()), "rlx_generate_f64_trace")
+    _call(states.device, "rlx_generate_f64_trace", states.data_ptr(), n, count, out.data_ptr(),
+          trace.data_ptr(), steps, p)
     return out, trace
 
 
@@ -432,23 +435,18 @@ class Plan:
             _check(lib().rlx_plan_create(ctypes.byref(self._h), req.ctypes.data, req.shape[0], lanes, seg_blocks,
                                          capacity_segments, _stream()), "rlx_plan_create")
         self.lanes, self.seg_blocks = lanes, seg_blocks
-        self.extent, self.records = self._extent(req)
+        self._read_needs()
 
-    @staticmethod
-    def _extent(req) -> tuple[int, int]:
-        """(output elements, records) the requests need: max of out_offset +
-        count and of state + 1 over requests with count > 0 (the library
-        accepted them, so these sums do not overflow)."""
-        live = req[req["count"] > 0]
-        if not live.shape[0]:
-            return 0, 0
-        return int((live["out_offset"] + live["count"]).max()), int(live["state"].max()) + 1
+    def _read_needs(self) -> None:
+        """Output elements and records the requests need."""
+        extent, records = _u64(0), _u64(0)
+        _check(lib().rlx_plan_needs(self._h, ctypes.byref(extent), ctypes.byref(records)), "rlx_plan_needs")
+        self.extent, self.records = extent.value, records.value
 
     def update(self, requests) -> None:
         req = _np.ascontiguousarray(requests, dtype=REQUEST_DTYPE)
-        with torch.cuda.device(self.device):
-            _check(lib().rlx_plan_update(self._h, req.ctypes.data, req.shape[0], _stream()), "rlx_plan_update")
-        self.extent, self.records = self._extent(req)
+        _call(self.device, "rlx_plan_update", self._h, req.ctypes.data, req.shape[0])
+        self._read_needs()
 
     def _check_out(self, states: torch.Tensor, out: torch.Tensor, dtype: torch.dtype, per_value: int) -> None:
         if _need_states(states) < self.records:
@@ -465,25 +463,19 @@ class Plan:
 
     def generate_f64(self, states: torch.Tensor, out: torch.Tensor) -> torch.Tensor:
         self._check_out(states, out, torch.float64, 1)
-        with torch.cuda.device(states.device):
-            _check(lib().rlx_plan_generate_f64(self._h, states.data_ptr(), out.data_ptr(), _stream()),
-                   "rlx_plan_generate_f64")
+        _call(states.device, "rlx_plan_generate_f64", self._h, states.data_ptr(), out.data_ptr())
         return out
 
     def generate_u64(self, states: torch.Tensor, out: torch.Tensor) -> torch.Tensor:
         self._check_out(states, out, torch.int64, 1)
-        with torch.cuda.device(states.device):
-            _check(lib().rlx_plan_generate_u64(self._h, states.data_ptr(), out.data_ptr(), _stream()),
-                   "rlx_plan_generate_u64")
+        _call(states.device, "rlx_plan_generate_u64", self._h, states.data_ptr(), out.data_ptr())
         return out
 
     def generate_f32(self, states: torch.Tensor, out: torch.Tensor) -> torch.Tensor:
         """Two floats per requested position: value j of a request goes to
         out[2 (out_offset + j)] and out[2 (out_offset + j) + 1]."""
         self._check_out(states, out, torch.float32, 2)
-        with torch.cuda.device(states.device):
-            _check(lib().rlx_plan_generate_f32(self._h, states.data_ptr(), out.data_ptr(), _stream()),
-                   "rlx_plan_generate_f32")
+        _call(states.device, "rlx_plan_generate_f32", self._h, states.data_ptr(), out.data_ptr())
         return out
 
     def close(self) -> None:

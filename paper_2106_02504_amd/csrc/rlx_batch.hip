@@ -66,13 +66,14 @@ static_assert(sizeof(Item) == 16, "item descriptor layout");
 // captured in a HIP graph replays whatever the plan holds at replay time.
 struct Header {
   uint32_t reserved;
-  uint32_t n_items;
+  uint32_t n_items;  // a multiple of GROUP; that many Items follow, then the Segments
   uint32_t pad[2];
   const uint32_t* C[MAX_LEVELS];  // folded multipliers A^(2^g) of each level
   const uint32_t* W[MAX_LEVELS];  // 16-bit window tables A^(j 65536^i) of each level
   const uint32_t* M[MAX_LEVELS];  // matrix-core step operands of each level
   uint32_t p[MAX_LEVELS];
 };
+static_assert(sizeof(Header) % 16 == 0, "items and segments stay aligned behind the header");
 
 // A plan with few items leaves most of the chip idle while one wave runs the
 // longest of them (256 requests up to 65 536 values: 264 items, the longest 64
@@ -100,10 +101,12 @@ __device__ __forceinline__ uint32_t part_blocks(uint32_t nblocks, uint32_t lgs, 
 }
 
 template <Out K, int LGS, bool MF>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MF ? 3 : 4))) void k_batch(const rlx_state* __restrict__ st,
-                                                 const Segment* __restrict__ segs,
-                                                 const Item* __restrict__ items, Header* __restrict__ hdr,
-                                                 uint64_t* __restrict__ out, uint32_t* __restrict__ err) {
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MF ? 3 : 4))) void k_batch(
+    const rlx_state* __restrict__ st, const Header* __restrict__ hdr, uint64_t* __restrict__ out,
+    uint32_t* __restrict__ err) {
+  // header, items and segments lie one after the other (upload)
+  const Item* __restrict__ items = reinterpret_cast<const Item*>(hdr + 1);
+  const Segment* __restrict__ segs = reinterpret_cast<const Segment*>(items + hdr->n_items);
   constexpr uint32_t G = 1u << LGS;
   constexpr bool SHARED = MF && LGS >= 5;  // a segment's lanes fill half-waves
   __shared__ __align__(16) uint64_t stage[BLOCK * SLOT_VALUES];
@@ -238,14 +241,11 @@ struct rlx_plan {
   uint32_t lanes = 0, lg = 0;
   uint64_t seg_blocks = 0;
   uint64_t cap = 0;  // segments (and items, with MAX_EMPTY more) the device buffers hold
-  Segment* d_segs = nullptr;
-  Item* d_items = nullptr;
-  Header* d_hdr = nullptr;
-  Segment* h_segs = nullptr;  // pinned staging for uploads
-  Item* h_items = nullptr;
-  Header* h_hdr = nullptr;
+  Header* d_hdr = nullptr;  // header, items, segments: one buffer, one copy per upload
+  Header* h_hdr = nullptr;  // pinned staging for it
   hipEvent_t uploaded = nullptr;
   uint64_t n_segs = 0, n_items = 0, total = 0;
+  uint64_t extent = 0, records = 0;
 };
 
 namespace {
@@ -255,6 +255,7 @@ struct Planned {
   std::vector<Item> items;
   std::vector<uint32_t> ps;  // luxury level of each slot
   uint64_t total = 0;
+  uint64_t extent = 0, records = 0;  // output elements and records the requests need
 };
 
 // Segments are laid out level by level; inside a level, the full segments
@@ -285,6 +286,8 @@ int plan_requests(const rlx_request* reqs, uint64_t n, uint32_t lg, uint64_t seg
     full_n[slot] += nb / seg_blocks;
     part_n[slot] += (nb % seg_blocks) != 0;
     pl.total += q.count;
+    pl.extent = std::max(pl.extent, q.out_offset + q.count);
+    pl.records = std::max(pl.records, q.state == UINT64_MAX ? q.state : q.state + 1);
   }
   const size_t levels = pl.ps.size();
   std::vector<uint64_t> full_at(levels), part_at(levels), part_end(levels);
@@ -393,35 +396,27 @@ int upload(rlx_plan* plan, const Planned& pl, hipStream_t s) {
   }
   // the previous upload must have left the staging buffers
   if (hipEventSynchronize(plan->uploaded) != hipSuccess) return RLX_EHIP;
-  const size_t n_items = group_items(pl.items, (uint32_t)plan->seg_blocks, plan->h_items);
+  Item* const items = reinterpret_cast<Item*>(plan->h_hdr + 1);
+  const size_t n_items = group_items(pl.items, (uint32_t)plan->seg_blocks, items);
   hd.n_items = (uint32_t)n_items;
   *plan->h_hdr = hd;
-  if (hipMemcpyAsync(plan->d_hdr, plan->h_hdr, sizeof(Header), hipMemcpyHostToDevice, s) != hipSuccess)
-    return RLX_EHIP;
-  if (!pl.segs.empty()) std::memcpy(plan->h_segs, pl.segs.data(), pl.segs.size() * sizeof(Segment));
-  if (!pl.segs.empty() &&
-      hipMemcpyAsync(plan->d_segs, plan->h_segs, pl.segs.size() * sizeof(Segment), hipMemcpyHostToDevice, s) !=
-          hipSuccess)
-    return RLX_EHIP;
-  if (!pl.items.empty() &&
-      hipMemcpyAsync(plan->d_items, plan->h_items, n_items * sizeof(Item), hipMemcpyHostToDevice, s) !=
-          hipSuccess)
-    return RLX_EHIP;
+  if (!pl.segs.empty())
+    std::memcpy(reinterpret_cast<Segment*>(items + n_items), pl.segs.data(), pl.segs.size() * sizeof(Segment));
+  const size_t bytes = sizeof(Header) + n_items * sizeof(Item) + pl.segs.size() * sizeof(Segment);
+  if (hipMemcpyAsync(plan->d_hdr, plan->h_hdr, bytes, hipMemcpyHostToDevice, s) != hipSuccess) return RLX_EHIP;
   if (hipEventRecord(plan->uploaded, s) != hipSuccess) return RLX_EHIP;
   plan->n_segs = pl.segs.size();
   plan->n_items = pl.items.size();
   plan->total = pl.total;
+  plan->extent = pl.extent;
+  plan->records = pl.records;
   return RLX_OK;
 }
 
 void free_plan(rlx_plan* p) {
   if (!p) return;
-  if (p->d_segs) (void)hipFree(p->d_segs);
-  if (p->d_items) (void)hipFree(p->d_items);
   if (p->d_hdr) (void)hipFree(p->d_hdr);
   if (p->h_hdr) (void)hipHostFree(p->h_hdr);
-  if (p->h_segs) (void)hipHostFree(p->h_segs);
-  if (p->h_items) (void)hipHostFree(p->h_items);
   if (p->uploaded) (void)hipEventDestroy(p->uploaded);
   delete p;
 }
@@ -454,11 +449,9 @@ int plan_launch(rlx_plan* plan, const rlx_state* states, void* out, void* stream
 #define RLX_BATCH(L)                                                                                      \
   case L:                                                                                                 \
     if (mf) {                                                                                             \
-      k_batch<K, L, true><<<(unsigned)blocks, BLOCK, 0, s>>>(states, plan->d_segs, plan->d_items, plan->d_hdr, \
-                                                              o, err);                                    \
+      k_batch<K, L, true><<<(unsigned)blocks, BLOCK, 0, s>>>(states, plan->d_hdr, o, err);                \
     } else {                                                                                              \
-      k_batch<K, L, false><<<(unsigned)blocks, BLOCK, 0, s>>>(states, plan->d_segs, plan->d_items,       \
-                                                               plan->d_hdr, o, err);                      \
+      k_batch<K, L, false><<<(unsigned)blocks, BLOCK, 0, s>>>(states, plan->d_hdr, o, err);               \
     }                                                                                                     \
     break;
   switch (plan->lg) {
@@ -496,12 +489,8 @@ int rlx_plan_create(rlx_plan** plan, const rlx_request* reqs, uint64_t n, uint32
   p->lg = lg;
   p->seg_blocks = seg_blocks;
   p->cap = std::max<uint64_t>({capacity_segments, (uint64_t)pl.segs.size(), 1});
-  if (hipMalloc(&p->d_segs, p->cap * sizeof(Segment)) != hipSuccess ||
-      hipMalloc(&p->d_items, (p->cap + MAX_EMPTY) * sizeof(Item)) != hipSuccess ||
-      hipMalloc(&p->d_hdr, sizeof(Header)) != hipSuccess ||
-      hipHostMalloc(&p->h_hdr, sizeof(Header), 0) != hipSuccess ||
-      hipHostMalloc(&p->h_segs, p->cap * sizeof(Segment), 0) != hipSuccess ||
-      hipHostMalloc(&p->h_items, (p->cap + MAX_EMPTY) * sizeof(Item), 0) != hipSuccess) {
+  const size_t bytes = sizeof(Header) + (p->cap + MAX_EMPTY) * sizeof(Item) + p->cap * sizeof(Segment);
+  if (hipMalloc(&p->d_hdr, bytes) != hipSuccess || hipHostMalloc(&p->h_hdr, bytes, 0) != hipSuccess) {
     free_plan(p);
     return RLX_ENOMEM;
   }
@@ -537,6 +526,13 @@ int rlx_plan_info(const rlx_plan* plan, uint64_t* segments, uint64_t* items, uin
   if (segments) *segments = plan->n_segs;
   if (items) *items = plan->n_items;
   if (total_values) *total_values = plan->total;
+  return RLX_OK;
+}
+
+int rlx_plan_needs(const rlx_plan* plan, uint64_t* extent, uint64_t* records) {
+  if (!plan) return RLX_EINVAL;
+  if (extent) *extent = plan->extent;
+  if (records) *records = plan->records;
   return RLX_OK;
 }
 
