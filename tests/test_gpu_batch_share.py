@@ -66,3 +66,27 @@ def test_more_items_than_shared_waves_and_update():
         o = int(req[k]["out_offset"])
         assert u[o:o + count].tolist() == O.window(O.seed(7 * s, p), p, start, count), k
     assert plan.info()["items"] == 7
+
+
+# header, items and segments up to 1 MiB (about 16 000 requests) go up through
+# a kernel, more through the copy engine; updates queue behind launches
+@pytest.mark.parametrize("first,second", ((1, 16000), (15900, 17000), (17000, 3), (16300, 16400)))
+def test_update_sizes(first, second):
+    rng = random.Random(first)
+    sets = [[(i % 40, rng.randrange(50), rng.randrange(1, 30), LEVELS[(i % 40) % 3]) for i in range(n)]
+            for n in (first, second)]
+    reqs = [rlx.requests_array(*(list(v) for v in zip(*s))) for s in sets]
+    st = records_to_tensor([(O.seed(7 * i, LEVELS[i % 3]), 0, LEVELS[i % 3]) for i in range(40)])
+    plan = rlx.Plan(reqs[0], capacity_segments=20000, lanes=64, seg_blocks=4096)
+    outs = []
+    for req in (reqs[0], reqs[1], reqs[0]):
+        plan.update(req)
+        outs.append(plan.generate_u64(st, torch.empty(plan.extent, dtype=torch.int64, device="cuda")))
+    assert rlx.check_errors() == 0
+    for (rs, req), out in zip(zip((sets[0], sets[1], sets[0]), (reqs[0], reqs[1], reqs[0])), outs):
+        u = out.cpu().numpy()
+        picks = {0, len(rs) - 1} | {rng.randrange(len(rs)) for _ in range(60)}
+        for k in picks:
+            s, start, count, p = rs[k]
+            o = int(req[k]["out_offset"])
+            assert u[o:o + count].tolist() == O.window(O.seed(7 * s, p), p, start, count), k
