@@ -275,7 +275,7 @@ __global__ __launch_bounds__(BLOCK) void k_init(rlx_state* __restrict__ st, uint
 // the block (offsets log-uniform over 64 bits: about 10 rounds per 4 waves
 // instead of 16).  Every thread of the block must call it; the order only
 // decides which lane handles which record.
-__device__ __forceinline__ uint64_t skip_record_index(const uint64_t* __restrict__ steps, uint64_t n,
+__device__ __forceinline__ uint32_t skip_record_index(const uint64_t* __restrict__ steps, uint64_t n,
                                                       int by_values, uint32_t per_step) {
   __shared__ uint32_t cnt[5];
   __shared__ uint32_t order[BLOCK];
@@ -290,29 +290,15 @@ __device__ __forceinline__ uint64_t skip_record_index(const uint64_t* __restrict
   for (uint32_t b = 0; b < key; ++b) base += cnt[b];
   order[base + slot] = threadIdx.x;
   __syncthreads();
-  return (uint64_t)blockIdx.x * BLOCK + order[threadIdx.x];
+  return order[threadIdx.x];
 }
 
-// by_values = 0: skip `steps` generator steps (pos unchanged); 1: skip that
-// many values of `per_step` values per step (pos + v = per_step k + pos',
-// k steps, new pos'): 12 for the 48-bit fields, 11 for the legacy 52-bit
-// values, whose records must have pos < 11.
-__global__ __launch_bounds__(BLOCK) void k_skip(rlx_state* __restrict__ st, uint64_t n,
-                                                const uint64_t* __restrict__ steps, uint64_t steps0,
-                                                uint32_t p, const uint32_t* __restrict__ W,
-                                                uint32_t* __restrict__ err, int by_values, uint32_t per_step) {
-  const uint64_t i = steps ? skip_record_index(steps, n, by_values, per_step)
-                           : (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  uint32_t x[NW], pos, sp;
-  load_record(st, i, x, pos, sp);
-  uint32_t bad = check_record(x, pos, sp, p);
-  if (by_values && pos >= per_step) bad |= RLX_ERR_BAD_POS;
-  if (bad) {
-    atomicOr(err, bad);
-    return;
-  }
-  uint64_t k = steps ? steps[i] : steps0;
+// The skip of one record: by_values = 0 skips `k` generator steps (pos
+// unchanged); 1 that many values of `per_step` values per step (pos + v =
+// per_step k + pos', k steps, new pos'): 12 for the 48-bit fields, 11 for the
+// legacy 52-bit values, whose records must have pos < 11.
+__device__ __forceinline__ void skip_record(uint32_t (&x)[NW], uint32_t& pos, uint64_t k, int by_values,
+                                            uint32_t per_step, const uint32_t* __restrict__ W) {
   if (by_values) {
     const uint64_t v = k;
     const uint32_t r = pos + (uint32_t)(v % per_step);
@@ -320,7 +306,39 @@ __global__ __launch_bounds__(BLOCK) void k_skip(rlx_state* __restrict__ st, uint
     pos = r % per_step;
   }
   skip_windows(x, k, W);
-  store_record(st, i, x, pos, sp);
+}
+
+// A block's 256 records pass through LDS as its waves' slabs (load_slab), and
+// leave when all of the block are done: in order of their skips' lengths any
+// lane may handle any of them.  2^20 records by log-uniform
+// offsets: 131 us with strided record accesses, 124 so (one offset: 100, 93;
+// 131 072 records: 23.4 and 14.8, now 21.7 and 13.2).
+__global__ __launch_bounds__(BLOCK) void k_skip(rlx_state* __restrict__ st, uint64_t n,
+                                                const uint64_t* __restrict__ steps, uint64_t steps0,
+                                                uint32_t p, const uint32_t* __restrict__ W,
+                                                uint32_t* __restrict__ err, int by_values, uint32_t per_step) {
+  __shared__ __align__(16) rlx_state slabs[BLOCK];
+  const uint32_t lane = threadIdx.x & 63u;
+  const uint32_t w0 = threadIdx.x & ~63u;
+  const uint64_t i0 = (uint64_t)blockIdx.x * BLOCK;
+  const uint32_t mine = n - i0 < BLOCK ? (uint32_t)(n - i0) : BLOCK;  // records of the block
+  const uint32_t wave = w0 < mine ? (mine - w0 < 64u ? mine - w0 : 64u) : 0u;  // and of the wave
+  load_slab(reinterpret_cast<uint4*>(slabs + w0), st, i0 + w0, wave, lane);
+  const uint32_t j = steps ? skip_record_index(steps, n, by_values, per_step) : threadIdx.x;
+  if (j < mine) {
+    uint32_t x[NW], pos, sp;
+    load_record(slabs, j, x, pos, sp);
+    uint32_t bad = check_record(x, pos, sp, p);
+    if (by_values && pos >= per_step) bad |= RLX_ERR_BAD_POS;
+    if (bad) {
+      atomicOr(err, bad);
+    } else {
+      skip_record(x, pos, steps ? steps[i0 + j] : steps0, by_values, per_step, W);
+      store_record(slabs, j, x, pos, sp);
+    }
+  }
+  if (steps) __syncthreads();
+  store_slab(st, reinterpret_cast<const uint4*>(slabs + w0), i0 + w0, wave == 64 ? ~0ull : (1ull << wave) - 1u, lane);
 }
 
 // Records of several luxury levels in one call (p = RLX_P_RECORD): the
@@ -360,7 +378,7 @@ __global__ __launch_bounds__(BLOCK) void k_skip_levels(rlx_state* __restrict__ s
                                                        const uint64_t* __restrict__ steps, uint64_t steps0,
                                                        LevelSet L, uint32_t* __restrict__ err, int by_values,
                                                        uint32_t per_step) {
-  const uint64_t i = steps ? skip_record_index(steps, n, by_values, per_step)
+  const uint64_t i = steps ? (uint64_t)blockIdx.x * BLOCK + skip_record_index(steps, n, by_values, per_step)
                            : (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   uint32_t x[NW], pos, sp;
@@ -372,14 +390,7 @@ __global__ __launch_bounds__(BLOCK) void k_skip_levels(rlx_state* __restrict__ s
     atomicOr(err, bad);
     return;
   }
-  uint64_t k = steps ? steps[i] : steps0;
-  if (by_values) {
-    const uint64_t v = k;
-    const uint32_t r = pos + (uint32_t)(v % per_step);
-    k = v / per_step + r / per_step;
-    pos = r % per_step;
-  }
-  skip_windows(x, k, level_ptr(L.W, li));
+  skip_record(x, pos, steps ? steps[i] : steps0, by_values, per_step, level_ptr(L.W, li));
   store_record(st, i, x, pos, sp);
 }
 
