@@ -293,37 +293,37 @@ __device__ __forceinline__ uint32_t skip_record_index(const uint64_t* __restrict
   return order[threadIdx.x];
 }
 
-// The skip of one record: by_values = 0 skips `k` generator steps (pos
+// The steps of one record's skip: by_values = 0 skips `k` generator steps (pos
 // unchanged); 1 that many values of `per_step` values per step (pos + v =
 // per_step k + pos', k steps, new pos'): 12 for the 48-bit fields, 11 for the
 // legacy 52-bit values, whose records must have pos < 11.
-__device__ __forceinline__ void skip_record(uint32_t (&x)[NW], uint32_t& pos, uint64_t k, int by_values,
-                                            uint32_t per_step, const uint32_t* __restrict__ W) {
+__device__ __forceinline__ uint64_t skip_steps(uint32_t& pos, uint64_t k, int by_values, uint32_t per_step) {
   if (by_values) {
     const uint64_t v = k;
     const uint32_t r = pos + (uint32_t)(v % per_step);
     k = v / per_step + r / per_step;
     pos = r % per_step;
   }
-  skip_windows(x, k, W);
+  return k;
 }
 
 // A block's 256 records pass through LDS as its waves' slabs (load_slab), and
 // leave when all of the block are done: in order of their skips' lengths any
-// lane may handle any of them.  2^20 records by log-uniform
-// offsets: 131 us with strided record accesses, 124 so (one offset: 100, 93;
-// 131 072 records: 23.4 and 14.8, now 21.7 and 13.2).
+// lane may handle any of them.  2^20 records by log-uniform offsets: 129 us
+// with strided record accesses, 117 so, at 5 waves per SIMD both (by one offset:
+// 99 us, 91; 131 072 records: 23.2 and 14.7, 21.6 and 13.2).  What is left is
+// vector issue, about 75 us of it, beside 300 MB of window entries from beyond
+// the L2.
 __global__ __launch_bounds__(BLOCK) void k_skip(rlx_state* __restrict__ st, uint64_t n,
                                                 const uint64_t* __restrict__ steps, uint64_t steps0,
                                                 uint32_t p, const uint32_t* __restrict__ W,
                                                 uint32_t* __restrict__ err, int by_values, uint32_t per_step) {
   __shared__ __align__(16) rlx_state slabs[BLOCK];
-  const uint32_t lane = threadIdx.x & 63u;
-  const uint32_t w0 = threadIdx.x & ~63u;
+  const uint32_t w0 = __builtin_amdgcn_readfirstlane(threadIdx.x & ~63u);
   const uint64_t i0 = (uint64_t)blockIdx.x * BLOCK;
   const uint32_t mine = n - i0 < BLOCK ? (uint32_t)(n - i0) : BLOCK;  // records of the block
   const uint32_t wave = w0 < mine ? (mine - w0 < 64u ? mine - w0 : 64u) : 0u;  // and of the wave
-  load_slab(reinterpret_cast<uint4*>(slabs + w0), st, i0 + w0, wave, lane);
+  load_slab(reinterpret_cast<uint4*>(slabs + w0), st, i0 + w0, wave, threadIdx.x & 63u);
   const uint32_t j = steps ? skip_record_index(steps, n, by_values, per_step) : threadIdx.x;
   if (j < mine) {
     uint32_t x[NW], pos, sp;
@@ -333,11 +333,16 @@ __global__ __launch_bounds__(BLOCK) void k_skip(rlx_state* __restrict__ st, uint
     if (bad) {
       atomicOr(err, bad);
     } else {
-      skip_record(x, pos, steps ? steps[i0 + j] : steps0, by_values, per_step, W);
-      store_record(slabs, j, x, pos, sp);
+      // only x and the steps stay in registers: 96 of them, 5 waves per SIMD
+      const uint64_t k = skip_steps(pos, steps ? steps[i0 + j] : steps0, by_values, per_step);
+      slabs[j].pos = pos;
+      skip_windows(x, k, W);
+      store_words(reinterpret_cast<uint32_t*>(&slabs[j]), x);
     }
   }
   if (steps) __syncthreads();
+  uint32_t lane = threadIdx.x & 63u;
+  asm("" : "+v"(lane));  // slab addresses are formed anew, not held through the skip
   store_slab(st, reinterpret_cast<const uint4*>(slabs + w0), i0 + w0, wave == 64 ? ~0ull : (1ull << wave) - 1u, lane);
 }
 
@@ -390,7 +395,7 @@ __global__ __launch_bounds__(BLOCK) void k_skip_levels(rlx_state* __restrict__ s
     atomicOr(err, bad);
     return;
   }
-  skip_record(x, pos, steps ? steps[i] : steps0, by_values, per_step, level_ptr(L.W, li));
+  skip_windows(x, skip_steps(pos, steps ? steps[i] : steps0, by_values, per_step), level_ptr(L.W, li));
   store_record(st, i, x, pos, sp);
 }
 
