@@ -2,10 +2,12 @@
 //
 // Kernels (one lane per stream record unless noted):
 //   k_tab_base / k_tab_fill / k_tab_fold / k_tab_win   per-luxury-level tables
-//   k_tab_mf_c / k_tab_mf_k / k_tab_mf_frag          matrix-core operands of a step
+//   k_tab_mf_c / k_tab_mf_k / k_tab_mf_frag / k_tab_start  matrix-core operands of a
+//                                          step and of the lane start-up
 //   k_init                                 seeding        (section 2.4)
 //   k_skip, k_skip_levels                  skip-ahead     (section 2.4)
 //   k_generate<U64|F64|NORMAL|F32, trace, LGS, MF> draw values (sections 2.1-2.3)
+//   k_generate_rows<K, T>                  the same, one lane per record through LDS
 //   k_generate_levels<K, LGS>              the same for records of several levels
 //   k_generate_lcg52<LGS, MF>              legacy raw-LCG doubles (section 2.3)
 //   k_test_*                               generic arithmetic for tests
@@ -1265,8 +1267,8 @@ uint32_t nominal_lanes(uint64_t n, uint64_t count, bool mf) {
 }
 
 // Lanes per record that generate calls with the matrix-core step take: the
-// power of two G with the
-// smallest estimate (microseconds) of the launch's time, up to 2^21 lanes.
+// power of two G with the smallest estimate (microseconds) of the launch's
+// time, up to 2^21 lanes.
 //  * Computing: a lane takes ceil(blocks / G) steps after a start-up worth
 //    3.5 steps (2..16 lanes: a generic product) or 2.75 (32 and more: shared
 //    by a half-wave; 1: none), and a step takes 1.15 us of latency or 0.65 us
@@ -1286,7 +1288,11 @@ uint32_t nominal_lanes(uint64_t n, uint64_t count, bool mf) {
 // with 16).  Records of several levels (Draw::LEVELS) count 2 below 32 lanes:
 // there a half-wave may mix levels, and its lanes then each run a generic
 // product a step, 4 steps' worth (30 000 x 1000 over five levels: 94 us with
-// 8 lanes and 64 with 32 in no order, 58 and 65 sorted by level).
+// 8 lanes and 64 with 32 in no order, 58 and 65 sorted by level).  Of their
+// 32-lane kernel a SIMD holds three waves, of the 64-lane one four: just over
+// one round of the former (6144 records and up to half as many again) is
+// slower than the latter (6400 x 4000: 62 us, 53; x 500: 19, 16.7; 8192 x
+// 1500: 30.5, 26.5; from 9500 records on they are even).
 enum class Draw { UNIFORM, NORMAL, LEVELS };
 
 uint32_t auto_lanes_mfma(uint64_t n, uint64_t count, Draw kind) {
@@ -1308,6 +1314,7 @@ uint32_t auto_lanes_mfma(uint64_t n, uint64_t count, Draw kind) {
       pick = g;
     }
   }
+  if (kind == Draw::LEVELS && pick == 32 && blocks > 32 && n > 6144 && n <= 9216) pick = 64;
   return (uint32_t)pick;
 }
 

@@ -117,3 +117,24 @@ def test_shared_start_next_to_rejected_records(G):
         else:
             vals, x2, pos2 = O.draws(x, pos, p, count)
             assert u[i].tolist() == vals and after[i] == (x2, pos2, p), i
+
+
+# records of several levels around one round of the 32-lane kernel's waves,
+# where calls that pick their own lanes go from 32 to 64 and back
+@pytest.mark.parametrize("n", (6144, 6145, 9216, 9217))
+@pytest.mark.parametrize("count", (370, 397))
+def test_levels_around_one_round(n, count):
+    levels = (24, 404, 2048)
+    rng = random.Random(n + count)
+    for p in levels:
+        rlx.prepare(p)
+    st = rlx.new_states(n)
+    for k, p in enumerate(levels):
+        st[k::3] = rlx.init_streams(rlx.new_states(st[k::3].shape[0]), p, id0=1000 * k)
+    u = rlx.generate_u64(st, count, rlx.P_RECORD)
+    assert rlx.check_errors() == 0
+    for i in [0, 1, 2, n - 1] + rng.sample(range(n), 20):
+        p = levels[i % 3]
+        x = O.seed(1000 * (i % 3) + i // 3, p)
+        assert u[i].tolist() == O.window(x, p, 0, count), i
+        assert tensor_to_records(st[i:i + 1]) == [O.state_at(x, p, count) + (p,)], i
