@@ -22,6 +22,10 @@ namespace rlx {
 //             for skips of k < 2^64 steps and for seeds with ids < 2^64, each
 //             entry the product of four entries of T (the kernels' own table;
 //             the device-side engine of rlx_engine.h uses T).
+//   P[g]      = matrix-core operands of a step by 2^g, g < MF_SPLIT_STEPS, for
+//             lanes that hold contiguous halves of a product (mfma_step_split);
+//             the engine's table M keeps the interleaved order, all 64 g.
+//   S         = matrix-core operands of A_p^l, l < 64: the lane start-up.
 constexpr int TAB_ROWS = RLX_TAB_ROWS;
 constexpr int TAB_COLS = RLX_TAB_COLS;
 constexpr int SEED_ROW0 = RLX_SEED_ROW0;  // 2^96 = 16^24
