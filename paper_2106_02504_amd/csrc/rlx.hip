@@ -311,7 +311,10 @@ __device__ __forceinline__ uint64_t skip_steps(uint32_t& pos, uint64_t k, int by
 
 // A block's 256 records pass through LDS as its waves' slabs (load_slab), and
 // leave when all of the block are done: in order of their skips' lengths any
-// lane may handle any of them.  2^20 records by log-uniform offsets: 129 us
+// lane may handle any of them.  A refused record (of another level, say, which
+// a call on another stream may be skipping meanwhile) is not written at all:
+// its copy's level is spoilt, and a wave stores the records whose copies have
+// level p.  2^20 records by log-uniform offsets: 129 us
 // with strided record accesses, 117 so, at 5 waves per SIMD both (by one offset:
 // 99 us, 91; 131 072 records: 23.2 and 14.7, 21.6 and 13.2).  What is left is
 // vector issue, about 75 us of it, beside 300 MB of window entries from beyond
@@ -334,8 +337,9 @@ __global__ __launch_bounds__(BLOCK) void k_skip(rlx_state* __restrict__ st, uint
     if (by_values && pos >= per_step) bad |= RLX_ERR_BAD_POS;
     if (bad) {
       atomicOr(err, bad);
+      slabs[j].p = ~p;  // not written back
     } else {
-      // only x and the steps stay in registers: 96 of them, 5 waves per SIMD
+      // only x and the steps stay in registers: 88 of them, 5 waves per SIMD
       const uint64_t k = skip_steps(pos, steps ? steps[i0 + j] : steps0, by_values, per_step);
       slabs[j].pos = pos;
       skip_windows(x, k, W);
@@ -343,9 +347,11 @@ __global__ __launch_bounds__(BLOCK) void k_skip(rlx_state* __restrict__ st, uint
     }
   }
   if (steps) __syncthreads();
+  wave_sync();
   uint32_t lane = threadIdx.x & 63u;
   asm("" : "+v"(lane));  // slab addresses are formed anew, not held through the skip
-  store_slab(st, reinterpret_cast<const uint4*>(slabs + w0), i0 + w0, wave == 64 ? ~0ull : (1ull << wave) - 1u, lane);
+  const uint64_t skipped = __ballot(lane < wave && slabs[w0 + lane].p == p);
+  store_slab(st, reinterpret_cast<const uint4*>(slabs + w0), i0 + w0, skipped, lane);
 }
 
 // Records of several luxury levels in one call (p = RLX_P_RECORD): the
