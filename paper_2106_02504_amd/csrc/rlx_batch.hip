@@ -15,7 +15,7 @@
 // cost, and the hardware dispatches waves in item order, so late waves get
 // short items (longest-processing-time order); long requests are cut so
 // that no item dominates the launch.  One wave per item (or a part of one,
-// share_log2), rather than persistent waves popping items from a counter,
+// item_share), rather than persistent waves popping items from a counter,
 // keeps the kernel's registers low: 118 VGPRs and 4 waves per SIMD.
 #include <hip/hip_runtime.h>
 
@@ -30,6 +30,7 @@
 #include "rlx_device.hpp"
 #include "rlx_internal.hpp"
 #include "rlx_mfma.hpp"
+#include "rlx_share.hpp"
 
 using namespace rlx;
 using namespace rlx::host;
@@ -75,31 +76,6 @@ struct Header {
 };
 static_assert(sizeof(Header) % 16 == 0, "items and segments stay aligned behind the header");
 
-// A plan with few items leaves most of the chip idle while one wave runs the
-// longest of them (256 requests up to 65 536 values: 264 items, the longest 64
-// iterations of a wave, 99 us of it), so the grid is at least MIN_WAVES waves
-// and spare ones share the items: 2^share_log2 waves an item, each taking a
-// run of at least MIN_SHARE iterations of every segment.  The item count is
-// read on the device, so a captured launch shares out whatever an update left.
-// That plan's launch takes 12 us this way, with planning and upload 39 us
-// instead of 99; 424 requests up to 2^19 values 36 us instead of 92.  A plan
-// of 8192 requests up to 2^20 values (19 000 items) shares nothing.
-constexpr uint32_t MIN_WAVES = 8192, MAX_SHARE_LOG2 = 6, MIN_SHARE = 2;
-
-__device__ __forceinline__ uint32_t share_log2(uint32_t n_items, uint32_t waves) {
-  uint32_t ls = 0;
-  while (ls < MAX_SHARE_LOG2 && n_items <= (waves >> (ls + 1))) ++ls;
-  return ls;
-}
-
-// Blocks of a segment of `nblocks` that each of 2^ls waves takes, in whole
-// iterations of 2^lgs blocks.
-__device__ __forceinline__ uint32_t part_blocks(uint32_t nblocks, uint32_t lgs, uint32_t ls) {
-  const uint32_t its = (nblocks + (1u << lgs) - 1u) >> lgs;
-  const uint32_t per = (its + (1u << ls) - 1u) >> ls;
-  return (per > MIN_SHARE || ls == 0 ? per : MIN_SHARE) << lgs;
-}
-
 template <Out K, int LGS, bool MF>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MF ? 3 : 4))) void k_batch(
     const rlx_state* __restrict__ st, const Header* __restrict__ hdr, uint64_t* __restrict__ out,
@@ -117,25 +93,38 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MF ? 3 : 
   const uint32_t l = lane & (G - 1);
   const uint32_t n_items = __builtin_amdgcn_readfirstlane(hdr->n_items);
   {
-    // waves (it << ls) .. + 2^ls - 1 of the grid share item `it`; the grid
-    // covers the plan's capacity, so waves past the current item count exit at
-    // once
+    // Waves part n_items + it, part < share, share item `it`; the item count is
+    // read here, so a captured launch shares out whatever an update left, and
+    // waves past the parts exit at once.  All first parts come first: short
+    // items have no others, and a launch of them is then the unshared one with
+    // empty waves behind it (with an item's waves side by side 1000 requests
+    // of 1024 values took 17 us against 10.6).
     const uint32_t wave = __builtin_amdgcn_readfirstlane(blockIdx.x * (BLOCK / WAVE) + tid_blk / WAVE);
-    const uint32_t ls = share_log2(n_items, gridDim.x * (BLOCK / WAVE));
-    const uint32_t it = wave >> ls, part = wave & ((1u << ls) - 1u);
-    if (it >= n_items) return;  // the whole block: items come in groups of four
+    const uint32_t share = item_share(n_items, gridDim.x * (BLOCK / WAVE));
+    if (wave >= n_items * share) return;  // the whole block: items come in groups of four
+    const uint32_t part = wave / n_items, it = wave % n_items;
     // MF: the block stages its level's matrix-core operands for A^G in LDS;
     // its items (group_items) and the waves that share one have one level.
     // (With mixed blocks, whose waves read their operands through the L1 and
     // so had the loop a second time in the code, 8192 requests up to 2^14
     // values took 47 us against 43, 3000 up to 2^18 123 us against 119, and
     // the kernel 146 VGPRs against 118.)
-    const uint32_t slot = __builtin_amdgcn_readfirstlane(items[it].slot);
+    const Item item = items[it];
+    const uint32_t slot = __builtin_amdgcn_readfirstlane(item.slot);
+    const uint32_t per = part_blocks(item.cost, LGS, share);
+    if (part != 0) {
+      // the parts of the block's four items are all empty
+      bool empty = true;
+      for (uint32_t q = 0; q < BLOCK / WAVE; ++q) {
+        const uint32_t cost = items[it - it % (BLOCK / WAVE) + q].cost;
+        empty = empty && part * part_blocks(cost, LGS, share) >= cost;
+      }
+      if (empty) return;
+    }
     if constexpr (MF) {
       mf_stage_operands(af_lds, hdr->M[slot] + (size_t)LGS * MF_LEVEL_WORDS, tid_blk, BLOCK);
       __syncthreads();
     }
-    const Item item = items[it];
     const uint32_t* __restrict__ ctabs = hdr->C[slot];
     const uint32_t* __restrict__ wtabs = hdr->W[slot];
     const uint32_t p = __builtin_amdgcn_readfirstlane(hdr->p[slot]);
@@ -149,7 +138,6 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MF ? 3 : 
     uint32_t w = 0;
     if (active) {
       const Segment& sg = segs[si];
-      const uint32_t per = part_blocks(sg.nblocks, LGS, ls);
       from = part * per;
       nblocks = from < sg.nblocks ? (sg.nblocks - from < per ? sg.nblocks - from : per) : 0u;
       active = nblocks != 0;
@@ -458,11 +446,11 @@ int plan_launch(rlx_plan* plan, const rlx_state* states, void* out, void* stream
   int rc = error_word(s, &err);
   if (rc) return rc;
   // One wave per item of a full plan (items never outnumber the segment
-  // capacity, plus the empty ones), and for small plans more (share_log2).  The grid depends only
-  // on the capacity, so a captured launch stays valid after updates; waves
-  // past the current item count exit.
+  // capacity, plus the empty ones), and for small plans more (item_share).
+  // The grid depends only on the capacity, so a captured launch stays valid
+  // after updates; waves past the current item count exit.
   const uint64_t waves =
-      std::max<uint64_t>(plan->cap + MAX_EMPTY, std::min<uint64_t>(MIN_WAVES, plan->cap << MAX_SHARE_LOG2));
+      std::max<uint64_t>(plan->cap + MAX_EMPTY, std::min<uint64_t>(SHARE_WAVES, plan->cap * MAX_SHARE));
   const uint64_t blocks = (waves + (BLOCK / WAVE) - 1) / (BLOCK / WAVE);
   if (blocks == 0 || blocks > 0x7FFFFFFFull) return RLX_EINVAL;
   uint64_t* o = reinterpret_cast<uint64_t*>(out);
