@@ -319,10 +319,13 @@ __device__ __forceinline__ void mf_settle(uint32_t (&x)[NW], int32_t p2, int32_t
 }
 
 // X <- A X mod m with operands in the split placement: fetch0 for the states
-// of lanes 0..31, fetch1 for lanes 32..63.  Must run with all 64 lanes of the
-// wave active; returns the canonical residue; `force_general` sends the end
-// of it through its general branch.
-template <class Fetch0, class Fetch1>
+// of lanes 0..31, fetch1 for lanes 32..63 (ONE: fetch0 for both).  Must run
+// with all 64 lanes of the wave active; returns the canonical residue;
+// `force_general` sends the end of it through its general branch.  With two
+// multipliers a tile's MFMAs of the one are issued before the other's operands
+// are read: 12 operand registers at a time, so that the levels kernels fit 128
+// VGPRs (both at once: 142, or 64 bytes of spills).
+template <bool ONE, class Fetch0, class Fetch1>
 __device__ __forceinline__ void mfma_step_split(uint32_t (&x)[NW], const Fetch0& fetch0, const Fetch1& fetch1,
                                                 bool force_general) {
   uint32_t a[9], b[9];
@@ -343,14 +346,27 @@ __device__ __forceinline__ void mfma_step_split(uint32_t (&x)[NW], const Fetch0&
   uint32_t t0 = 0, t1 = 0;
 #pragma unroll
   for (int mt = 0; mt < 3; ++mt) {
-    const mf_v4i f0 = fetch0(3 * mt), f1 = fetch0(3 * mt + 1), f2 = fetch0(3 * mt + 2);
-    const mf_v4i g0 = fetch1(3 * mt), g1 = fetch1(3 * mt + 1), g2 = fetch1(3 * mt + 2);
-    mf_v16i s0 = __builtin_amdgcn_mfma_i32_32x32x32_i8(f0, b0[0], zero, 0, 0, 0);
-    mf_v16i s1 = __builtin_amdgcn_mfma_i32_32x32x32_i8(g0, b1[0], zero, 0, 0, 0);
-    s0 = __builtin_amdgcn_mfma_i32_32x32x32_i8(f1, b0[1], s0, 0, 0, 0);
-    s1 = __builtin_amdgcn_mfma_i32_32x32x32_i8(g1, b1[1], s1, 0, 0, 0);
-    s0 = __builtin_amdgcn_mfma_i32_32x32x32_i8(f2, b0[2], s0, 0, 0, 0);
-    s1 = __builtin_amdgcn_mfma_i32_32x32x32_i8(g2, b1[2], s1, 0, 0, 0);
+    mf_v16i s0, s1;
+    if constexpr (ONE) {
+      const mf_v4i f0 = fetch0(3 * mt), f1 = fetch0(3 * mt + 1), f2 = fetch0(3 * mt + 2);
+      s0 = __builtin_amdgcn_mfma_i32_32x32x32_i8(f0, b0[0], zero, 0, 0, 0);
+      s1 = __builtin_amdgcn_mfma_i32_32x32x32_i8(f0, b1[0], zero, 0, 0, 0);
+      s0 = __builtin_amdgcn_mfma_i32_32x32x32_i8(f1, b0[1], s0, 0, 0, 0);
+      s1 = __builtin_amdgcn_mfma_i32_32x32x32_i8(f1, b1[1], s1, 0, 0, 0);
+      s0 = __builtin_amdgcn_mfma_i32_32x32x32_i8(f2, b0[2], s0, 0, 0, 0);
+      s1 = __builtin_amdgcn_mfma_i32_32x32x32_i8(f2, b1[2], s1, 0, 0, 0);
+    } else {
+      __builtin_amdgcn_sched_barrier(0);
+      const mf_v4i f0 = fetch0(3 * mt), f1 = fetch0(3 * mt + 1), f2 = fetch0(3 * mt + 2);
+      s0 = __builtin_amdgcn_mfma_i32_32x32x32_i8(f0, b0[0], zero, 0, 0, 0);
+      s0 = __builtin_amdgcn_mfma_i32_32x32x32_i8(f1, b0[1], s0, 0, 0, 0);
+      s0 = __builtin_amdgcn_mfma_i32_32x32x32_i8(f2, b0[2], s0, 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      const mf_v4i g0 = fetch1(3 * mt), g1 = fetch1(3 * mt + 1), g2 = fetch1(3 * mt + 2);
+      s1 = __builtin_amdgcn_mfma_i32_32x32x32_i8(g0, b1[0], zero, 0, 0, 0);
+      s1 = __builtin_amdgcn_mfma_i32_32x32x32_i8(g1, b1[1], s1, 0, 0, 0);
+      s1 = __builtin_amdgcn_mfma_i32_32x32x32_i8(g2, b1[2], s1, 0, 0, 0);
+    }
 #pragma unroll
     for (int q = 0; q < (mt < 2 ? 4 : 2); ++q) {
       const int j = 4 * mt + q;
@@ -387,7 +403,7 @@ __device__ __forceinline__ void mfma_step_split(uint32_t (&x)[NW], const Fetch0&
 
 template <class Fetch>
 __device__ __forceinline__ void mfma_step_split(uint32_t (&x)[NW], const Fetch& fetch, bool force_general) {
-  mfma_step_split(x, fetch, fetch, force_general);
+  mfma_step_split<true>(x, fetch, fetch, force_general);
 }
 
 // ---------------------------------------------------------------------------

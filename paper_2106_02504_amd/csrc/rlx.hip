@@ -719,12 +719,15 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(T == 1 ? 
 // L1, as the batched kernel does for items of mixed levels).  With fewer
 // lanes a wave whose halves each hold one level steps the same way, and a
 // wave with mixed levels inside a half multiplies each lane by its own level's
-// A^G with the generic multiplication.  3 waves per SIMD but for 64 lanes:
-// with two multipliers in flight 4 waves spill (65 536 x 4096 in no order 488
-// us against 447; 8192 x 1000: 25.1 against 26.3, and 43.8 with the 8 lanes
-// taken before).
+// A^G with the generic multiplication.  4 waves per SIMD (3 for normals at 1
+// and 64 lanes), with at most 16 bytes of spills below 32 lanes and none above;
+// with 3 (both multipliers' operands read at once) 32 lanes took, in level
+// blocks and in no order, 65 536 x 4096: 440 and 466 us against 411 and 442,
+// 30 000 x 1000: 66.6 and 72.1 against 62.4 and 65.3, 8192 x 1000: 23.7 and
+// 24.6 against 20.8 and 21.2.  A block's operands staged in LDS where it has
+// one level are no gain beside the L1 (388, 455; 62.7, 66.3; 21.9, 21.9).
 template <Out K, int LGS>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(K == Out::NORMAL || LGS < 6 ? 3 : 4))) void k_generate_levels(
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(K == Out::NORMAL && (LGS == 0 || LGS == 6) ? 3 : 4))) void k_generate_levels(
     rlx_state* __restrict__ st, uint32_t n, uint64_t count, uint64_t* __restrict__ out, LevelSet L, uint32_t lg,
     uint32_t* __restrict__ err) {
   constexpr bool STAGED = LGS > 0;
@@ -793,7 +796,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(K == Out:
     const uint32_t t = l + (k << lg);
     const bool live = active && t <= nadv;
     if (!__any(live)) break;
-    if (live && t == nadv) store_record(st, i, x, (uint32_t)((pos + count) % FIELDS), sp);
+    if (live && t == nadv) store_state(st, i, x, (uint32_t)((pos + count) % FIELDS));
     uint64_t* const row = out + (uint64_t)i * count;
     if (!STAGED) {
       uint32_t d[NW];
@@ -817,8 +820,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(K == Out:
         // one level for the wave: one operand fetch serves both halves
         mfma_step_split(x, MfFromBuffer(level_ptr(L.M, u0) + (size_t)lg * MF_LEVEL_WORDS, threadIdx.x & 63), false);
       } else if (SHARED || uniform) {
-        mfma_step_split(x, MfFromBuffer(level_ptr(L.M, u0) + (size_t)lg * MF_LEVEL_WORDS, threadIdx.x & 63),
-                        MfFromBuffer(level_ptr(L.M, u1) + (size_t)lg * MF_LEVEL_WORDS, threadIdx.x & 63), false);
+        mfma_step_split<false>(x, MfFromBuffer(level_ptr(L.M, u0) + (size_t)lg * MF_LEVEL_WORDS, threadIdx.x & 63),
+                               MfFromBuffer(level_ptr(L.M, u1) + (size_t)lg * MF_LEVEL_WORDS, threadIdx.x & 63), false);
       } else if (!SHARED && active) {
         uint32_t a[NW];
         load_words(level_ptr(L.C, li) + (size_t)lg * FOLD_ROW_WORDS, a);  // C_0 = A^G
@@ -1294,11 +1297,7 @@ uint32_t nominal_lanes(uint64_t n, uint64_t count, bool mf) {
 // with 16).  Records of several levels (Draw::LEVELS) count 2 below 32 lanes:
 // there a half-wave may mix levels, and its lanes then each run a generic
 // product a step, 4 steps' worth (30 000 x 1000 over five levels: 94 us with
-// 8 lanes and 64 with 32 in no order, 58 and 65 sorted by level).  Of their
-// 32-lane kernel a SIMD holds three waves, of the 64-lane one four: just over
-// one round of the former (6144 records and up to half as many again) is
-// slower than the latter (6400 x 4000: 62 us, 53; x 500: 19, 16.7; 8192 x
-// 1500: 30.5, 26.5; from 9500 records on they are even).
+// 8 lanes and 64 with 32 in no order, 58 and 65 sorted by level).
 enum class Draw { UNIFORM, NORMAL, LEVELS };
 
 uint32_t auto_lanes_mfma(uint64_t n, uint64_t count, Draw kind) {
@@ -1320,7 +1319,6 @@ uint32_t auto_lanes_mfma(uint64_t n, uint64_t count, Draw kind) {
       pick = g;
     }
   }
-  if (kind == Draw::LEVELS && pick == 32 && blocks > 32 && n > 6144 && n <= 9216) pick = 64;
   return (uint32_t)pick;
 }
 

@@ -107,6 +107,17 @@ __device__ __forceinline__ uint32_t check_record(const uint32_t (&x)[NW], uint32
   return bad;
 }
 
+// store_record for a record that keeps its level: the level is not written, so
+// it need not be held until then.
+__device__ __forceinline__ void store_state(rlx_state* __restrict__ st, uint64_t i, const uint32_t (&x)[NW],
+                                            uint32_t pos) {
+  uint4* const r = reinterpret_cast<uint4*>(st + i);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) r[q] = make_uint4(x[4 * q], x[4 * q + 1], x[4 * q + 2], x[4 * q + 3]);
+  *reinterpret_cast<uint2*>(r + 4) = make_uint2(x[16], x[17]);
+  st[i].pos = pos;
+}
+
 // Word rr of record i (0 from word 18 on) and the record's position and
 // level, for a half-wave whose lanes share the record; without a record
 // (active false) the state 1.
