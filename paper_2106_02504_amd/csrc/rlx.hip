@@ -589,8 +589,22 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(K == Out:
 // (T = 2, 51 us instead of 65 at 24 values before rows were kept whole); with
 // up to 12 the smaller stage (T = 1) leaves twice the waves (2^20 x 12: 63 us
 // against 80).  Rows that end within the kept steps go out as the one run of
-// whole lines they are, for any count and positions.
+// whole lines they are, for any count and positions.  With T = 1 records take
+// one step or none: those that took it leave through LDS at the end whatever
+// their positions, of the others only the position is written (2^20 x 1 at
+// mixed positions 51.5 us with whole records stored by their lanes, 37.4 so).
 constexpr uint64_t ROWS_MAX_COUNT = 1ull << 20;  // 32-bit byte offsets within a wave's 64 rows
+// From how many records on the kernel is worth it, and with T = 1 a wave whose
+// records have several positions, or odd ones, stores joined runs rather than
+// each lane its own values.  Below, waves are few and what counts is the chain
+// of one wave's instructions, where k_generate's direct stores are shorter:
+// 1000 records x 25 in 6.8 us against 11.5, 33 000 x 24 in 9.2 and 8.8, 65 000 x
+// 24 in 12.9 and 9.2.  Normals in rows of less than a step it beats for longer,
+// as it transforms only the fields that some lane wants: 105 000 x 3 in 7.9 us
+// and 9.8, 262 144 x 3 even.  Joined runs against each lane's own, at mixed
+// positions: 65 000 x 5 in 7.5 us and 6.0, 140 000 x 11 10.1 and 12.6.
+constexpr uint64_t ROWS_MIN = 1u << 15, ROWS_MIN_SHORT_NORMALS = 1u << 18;
+constexpr uint32_t ROWS_JOINED = 1u << 17;
 
 template <Out K, uint32_t T>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(T == 1 ? 4 : 2))) void k_generate_rows(
@@ -630,6 +644,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(T == 1 ? 
   const uint32_t pos0 = __builtin_amdgcn_readfirstlane(__shfl(pos, __ffsll((unsigned long long)act) - 1));
   const bool same = __all(!active || pos == pos0);
   const bool aligned16 = (reinterpret_cast<uintptr_t>(out) & 15) == 0;
+  // the wave's last step; records stop there or one step before
+  const uint32_t last = count / FIELDS + (__any(active && pos + count >= FIELDS * (count / FIELDS + 1)) ? 1u : 0u);
   const bool pairs = same && (pos0 & 1u) == 0 && (count & 1u) == 0 && aligned16;
   uint64_t* const rows = out + (uint64_t)iw * count;
   wave_sync();
@@ -678,6 +694,11 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(T == 1 ? 
             if (j < count && ((act >> rec) & 1u) != 0)
               store_pair<false>(rows + (rec * count + j), reinterpret_cast<const ulonglong2*>(slab)[rec * (SLOT / 2) + f]);
           }
+        } else if (T == 1 && n < ROWS_JOINED) {
+          const uint32_t j = FIELDS * k0 - ps;
+#pragma unroll
+          for (uint32_t f = 0; f < RUN; ++f)
+            if (mine && j + f < count) rows[v * count + (j + f)] = slab[v * SLOT + f];
         } else {
 #pragma unroll 4
           for (uint32_t q = 0; q < RUN; ++q) {
@@ -690,8 +711,10 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(T == 1 ? 
       }
     }
     if (mine && k == nadv) {
-      if (same) {
+      if (T == 1 ? k == last : same) {
         store_record(reinterpret_cast<rlx_state*>(slab), v, x, (ps + count) % FIELDS, p);
+      } else if (T == 1 && k == 0) {
+        st[iw + v].pos = ps + count;  // the state has not moved
       } else {
         store_record(st, iw + v, x, (ps + count) % FIELDS, p);
       }
@@ -700,13 +723,14 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(T == 1 ? 
       mfma_step_split(x, MfFromArray{af, v}, false);
     }
   }
-  if (same) {
-    // the records were all written to LDS in the last iteration
+  if (T == 1 || same) {
+    // the records of the last iteration are in LDS
     wave_sync();
+    const uint64_t moved = T == 1 ? __ballot(active && (pos + count) / FIELDS == last) : act;
 #pragma unroll
     for (uint32_t q = 0; q < 5; ++q) {
       const uint32_t e = 64u * q + lane;
-      if (((act >> (e / 5u)) & 1u) != 0) recs[e] = slab4[e];
+      if (((moved >> (e / 5u)) & 1u) != 0) recs[e] = slab4[e];
     }
   }
 }
@@ -1438,7 +1462,8 @@ int generate_impl(rlx_state* states, uint64_t n, uint64_t count, void* out, uint
   const uint32_t lgs = lg < 6 ? lg : 6;
   const int writeback = lg <= 6;
   const bool mf = g_step_kind.load(std::memory_order_relaxed) == RLX_STEP_MFMA;
-  if (!TRACE && lgs == 0 && mf && !force_general && count <= ROWS_MAX_COUNT) {
+  if (!TRACE && lgs == 0 && mf && !force_general && count <= ROWS_MAX_COUNT &&
+      n >= (K == Out::NORMAL && count < FIELDS ? ROWS_MIN_SHORT_NORMALS : ROWS_MIN)) {
     if (count <= FIELDS) {
       k_generate_rows<K, 1><<<grid, BLOCK, 0, s>>>(states, (uint32_t)n, (uint32_t)count, o, t.P, p, err);
     } else {
