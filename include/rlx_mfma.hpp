@@ -325,7 +325,7 @@ __device__ __forceinline__ void mf_settle(uint32_t (&x)[NW], int32_t p2, int32_t
 // multipliers a tile's MFMAs of the one are issued before the other's operands
 // are read: 12 operand registers at a time, so that the levels kernels fit 128
 // VGPRs (both at once: 142, or 64 bytes of spills).
-template <bool ONE, class Fetch0, class Fetch1>
+template <bool ONE, int CROSS, class Fetch0, class Fetch1>
 __device__ __forceinline__ void mfma_step_split(uint32_t (&x)[NW], const Fetch0& fetch0, const Fetch1& fetch1,
                                                 bool force_general) {
   uint32_t a[9], b[9];
@@ -380,9 +380,7 @@ __device__ __forceinline__ void mfma_step_split(uint32_t (&x)[NW], const Fetch0&
         t1 = w1;  // word 18
       }
     }
-    // the first tile's words before the last tile's MFMAs: 120 VGPRs in the
-    // staged generate kernels against 128 and spills for normals
-    if (mt == 0) __builtin_amdgcn_sched_barrier(0);
+    if (mt == 0) __builtin_amdgcn_sched_barrier(ONE ? CROSS : 0);
   }
   // t0 (signed) enters at word 9, t1 = h (< 2^15) is folded with 2^576 =
   // 2^240 - 1: - h at word 0, + (h << 16) at word 7.  Each sum is carried two
@@ -401,9 +399,17 @@ __device__ __forceinline__ void mfma_step_split(uint32_t (&x)[NW], const Fetch0&
     mf_settle(x, -(int32_t)br, (int32_t)cy, (int32_t)p11, (int32_t)t1 >> 31);
 }
 
-template <class Fetch>
+// What may be moved across the end of the first tile: MFMAs and LDS reads of the
+// next tiles, or LDS reads only, where 128 VGPRs hold no more (normals, levels,
+// batches).  With
+// nothing moved a step of a lone wave takes 5% longer: 64 streams x 10 000 at 8
+// lanes 130 us against 124 (normals 248, 245 with LDS reads, 250 and spills with
+// MFMAs); 65 536 x 4096 is even.
+constexpr int MF_CROSS_ALL = 0x108, MF_CROSS_LDS = 0x100;
+
+template <int CROSS = MF_CROSS_ALL, class Fetch>
 __device__ __forceinline__ void mfma_step_split(uint32_t (&x)[NW], const Fetch& fetch, bool force_general) {
-  mfma_step_split<true>(x, fetch, fetch, force_general);
+  mfma_step_split<true, CROSS>(x, fetch, fetch, force_general);
 }
 
 // ---------------------------------------------------------------------------

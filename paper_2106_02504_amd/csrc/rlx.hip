@@ -437,6 +437,9 @@ __device__ __forceinline__ void start_shared(uint32_t (&x)[NW], uint32_t w, uint
   wave_sync();
 }
 
+template <Out K>
+constexpr int STEP_CROSS = K == Out::NORMAL ? MF_CROSS_LDS : MF_CROSS_ALL;
+
 // Draw `count` values for every record with G = 2^lg lanes per record.
 //
 // Block t of a record is the t-th LCG state visited (t = 0 is the state on
@@ -565,7 +568,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(K == Out:
     }
     if (__any(live && t + (1u << lg) <= nadv)) {
       if constexpr (MF) {
-        mfma_step_split(x, MfFromArray{af, threadIdx.x & 63}, force);
+        mfma_step_split<STEP_CROSS<K>>(x, MfFromArray{af, threadIdx.x & 63}, force);
       } else {
         step(x, constant_table(ctab), force, SgprBarrier());
       }
@@ -720,7 +723,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(T == 1 ? 
       }
     }
     if (__any(mine && k < nadv)) {
-      mfma_step_split(x, MfFromArray{af, v}, false);
+      mfma_step_split<STEP_CROSS<K>>(x, MfFromArray{af, v}, false);
     }
   }
   if (T == 1 || same) {
@@ -842,10 +845,10 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(K == Out:
     if (__any(live && t + (1u << lg) <= nadv)) {
       if (LGS == 6 || (uniform && u0 == u1)) {
         // one level for the wave: one operand fetch serves both halves
-        mfma_step_split(x, MfFromBuffer(level_ptr(L.M, u0) + (size_t)lg * MF_LEVEL_WORDS, threadIdx.x & 63), false);
+        mfma_step_split<MF_CROSS_LDS>(x, MfFromBuffer(level_ptr(L.M, u0) + (size_t)lg * MF_LEVEL_WORDS, threadIdx.x & 63), false);
       } else if (SHARED || uniform) {
-        mfma_step_split<false>(x, MfFromBuffer(level_ptr(L.M, u0) + (size_t)lg * MF_LEVEL_WORDS, threadIdx.x & 63),
-                               MfFromBuffer(level_ptr(L.M, u1) + (size_t)lg * MF_LEVEL_WORDS, threadIdx.x & 63), false);
+        mfma_step_split<false, 0>(x, MfFromBuffer(level_ptr(L.M, u0) + (size_t)lg * MF_LEVEL_WORDS, threadIdx.x & 63),
+                                  MfFromBuffer(level_ptr(L.M, u1) + (size_t)lg * MF_LEVEL_WORDS, threadIdx.x & 63), false);
       } else if (!SHARED && active) {
         uint32_t a[NW];
         load_words(level_ptr(L.C, li) + (size_t)lg * FOLD_ROW_WORDS, a);  // C_0 = A^G

@@ -210,7 +210,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MF ? 3 : 
       group_store<LGS>(stage, tid_blk, l, u0, span, active, base);
       if (__any(live && t + G < nblocks)) {
         if constexpr (MF) {
-          mfma_step_split(x, MfFromArray{af_lds, lane}, false);
+          mfma_step_split<MF_CROSS_LDS>(x, MfFromArray{af_lds, lane}, false);
         } else {
           step(x, constant_table(ctab), false, SgprBarrier());
         }
