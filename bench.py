@@ -616,7 +616,7 @@ def main() -> int:
     rlx.set_step_kernel(kind)
     rlx.prepare(P)
     rlx.set_lanes_per_stream(args.lanes)
-    lanes = rlx.lanes_per_stream(N_STREAMS, DRAWS)
+    lanes = rlx.call_lanes("uniform", N_STREAMS, DRAWS)
     st = rlx.new_states(N_STREAMS, device=dev)
     out = torch.empty((N_STREAMS, DRAWS), dtype=torch.float64, device=dev)
     total = N_STREAMS * DRAWS
@@ -729,7 +729,7 @@ def main() -> int:
                           # the generate call alone (its kernel and, for a record that
                           # spans several waves, the skip launch advancing it)
                           "call_ms": k1, "call_value": (1 << 20) / (k1 * 1e-3),
-                          "lanes_per_stream": rlx.lanes_per_stream(1, 1 << 20),
+                          "lanes_per_stream": rlx.call_lanes("traced", 1, 1 << 20),
                           "one_lane_ms": dt1 * 1e3, "one_lane_us_per_generator_step": dt1 * 1e6 / steps1,
                           "workload": "1 stream (id 1), p=2048, 2^20 doubles + state after each step"}
     if "skip" in wanted:
@@ -824,7 +824,7 @@ def main() -> int:
         rlx.set_lanes_per_stream(0)
         alt = run_steps(max(5, args.warmup // 2), max(5, args.steps // 2))
         legs["step_valu" if other == rlx.STEP_VALU else "step_mfma"] = dict(
-            alt, unit="doubles/s", lanes_per_stream=rlx.lanes_per_stream(N_STREAMS, DRAWS),
+            alt, unit="doubles/s", lanes_per_stream=rlx.call_lanes("uniform", N_STREAMS, DRAWS),
             same_values=bool(torch.equal(out, ref_out)))
         del ref_out
         rlx.set_step_kernel(kind)

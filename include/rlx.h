@@ -332,14 +332,28 @@ int rlx_import_ranlux(rlx_state *states, uint64_t n, const uint64_t *packed,
  * advancing by the launch-uniform multiplier A_p^G), and their values are
  * staged through LDS so that stores write contiguous runs of the output row.
  * By default a call picks G from n, count and the kind of draw, by an estimate
- * of its time; rlx_lanes_per_stream reports the nominal number, the most
- * lanes up to 2^21 in all that leave each at least 8 steps (2^20 and 16 with
- * the vector-ALU step; one step while there are fewer than 2^16 lanes), from
- * which a call's own pick may differ.  rlx_set_lanes_per_stream(G) forces a
- * power of two G <= RLX_MAX_LANES for all later calls in the process, and is
- * then what rlx_lanes_per_stream reports (0 restores the automatic pick).
- * The values produced never depend on G. */
+ * of its time; rlx_call_lanes reports the pick.  rlx_set_lanes_per_stream(G)
+ * forces a power of two G <= RLX_MAX_LANES for all later calls in the process
+ * (0 restores the automatic pick).  The values produced never depend on G. */
 int rlx_set_lanes_per_stream(uint32_t lanes);
+
+/* G that a generate call of one kind takes now (forced lanes and the step
+ * kernel included) for n records and `count` positions each (half of
+ * rlx_generate_f32's floats): 48-bit draws of any width, normals, either of
+ * them for records of several levels (RLX_P_RECORD; at most 64),
+ * rlx_generate_f64_lcg52, rlx_generate_f64_trace.  0 for any other kind. */
+#define RLX_DRAW_UNIFORM 0
+#define RLX_DRAW_NORMAL 1
+#define RLX_DRAW_LEVELS 2
+#define RLX_DRAW_LEVELS_NORMAL 3
+#define RLX_DRAW_LEGACY 4
+#define RLX_DRAW_TRACED 5
+uint32_t rlx_call_lanes(int kind, uint64_t n, uint64_t count);
+
+/* The nominal number of lanes: the forced one, or the most lanes up to 2^21 in
+ * all that leave each at least 8 steps (2^20 and 16 with the vector-ALU step;
+ * one step while there are fewer than 2^16 lanes).  Calls with the vector-ALU
+ * step take it; those with the matrix-core step pick by rlx_call_lanes. */
 uint32_t rlx_lanes_per_stream(uint64_t n, uint64_t count);
 
 /* How the generate calls (rlx_generate_f64, _u64, _f32, _normal_f64,

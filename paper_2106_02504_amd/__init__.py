@@ -26,7 +26,7 @@ __all__ = [
     "RlxError", "lib", "new_states", "prepare", "init_streams", "skip",
     "generate_f64", "generate_u64", "generate_normal_f64", "generate_f64_trace", "check_errors",
     "EngineTables", "get_tables", "build_tables_static", "table_words", "test_engine",
-    "set_lanes_per_stream", "lanes_per_stream", "set_step_kernel", "step_kernel", "STEP_MFMA", "STEP_VALU",
+    "set_lanes_per_stream", "lanes_per_stream", "call_lanes", "DRAW_KINDS", "set_step_kernel", "step_kernel", "STEP_MFMA", "STEP_VALU",
     "skip_values", "export_ranlux", "import_ranlux", "REQUEST_DTYPE", "requests_array", "Plan", "plan_dry_run",
     "constants", "test_mulmod", "test_pow", "test_to_ranlux",
     "test_generate_u64_general", "test_step", "test_rates", "RATE_KINDS", "STATE_WORDS",
@@ -62,6 +62,7 @@ _SIGS = {
     "rlx_check_errors": (_int, [_vp, ctypes.POINTER(_u32)]),
     "rlx_set_lanes_per_stream": (_int, [_u32]),
     "rlx_lanes_per_stream": (_u32, [_u64, _u64]),
+    "rlx_call_lanes": (_u32, [_int, _u64, _u64]),
     "rlx_set_step_kernel": (_int, [_int]),
     "rlx_step_kernel": (_int, []),
     "rlx_constants": (None, [ctypes.POINTER(_u32), ctypes.POINTER(_u32)]),
@@ -380,8 +381,18 @@ def set_lanes_per_stream(lanes: int) -> None:
 
 def lanes_per_stream(n: int, count: int) -> int:
     """The nominal number of lanes per record for n records and `count` values
-    (the forced one, if any); a generate call's own pick may differ."""
+    (the forced one, if any); what a call takes is call_lanes."""
     return int(lib().rlx_lanes_per_stream(n, count))
+
+
+# kinds of draw by the number the library gives them
+DRAW_KINDS = {"uniform": 0, "normal": 1, "levels": 2, "levels_normal": 3, "legacy": 4, "traced": 5}
+
+
+def call_lanes(kind: str, n: int, count: int) -> int:
+    """The lanes per record that a generate call of this kind takes now for n
+    records and `count` positions each (float32: half of its floats)."""
+    return int(lib().rlx_call_lanes(DRAW_KINDS[kind], n, count))
 
 
 STEP_MFMA = 0   # generator step on the int8 matrix cores (default)

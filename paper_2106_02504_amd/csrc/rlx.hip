@@ -1741,6 +1741,13 @@ uint32_t rlx_lanes_per_stream(uint64_t n, uint64_t count) {
   return o ? o : nominal_lanes(n, count, g_step_kind.load(std::memory_order_relaxed) == RLX_STEP_MFMA);
 }
 
+uint32_t rlx_call_lanes(int kind, uint64_t n, uint64_t count) {
+  if (kind < RLX_DRAW_UNIFORM || kind > RLX_DRAW_TRACED) return 0;
+  const bool levels = kind == RLX_DRAW_LEVELS || kind == RLX_DRAW_LEVELS_NORMAL;
+  const uint32_t g = lanes_for(n, count, levels ? Draw::LEVELS : kind == RLX_DRAW_NORMAL ? Draw::NORMAL : Draw::UNIFORM);
+  return levels && g > 64 ? 64 : g;
+}
+
 int rlx_set_step_kernel(int kind) {
   if (kind != RLX_STEP_MFMA && kind != RLX_STEP_VALU) return RLX_EINVAL;
   g_step_kind.store(kind, std::memory_order_relaxed);
