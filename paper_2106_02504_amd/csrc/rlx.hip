@@ -602,11 +602,19 @@ constexpr uint64_t ROWS_MAX_COUNT = 1ull << 20;  // 32-bit byte offsets within a
 // each lane its own values.  Below, waves are few and what counts is the chain
 // of one wave's instructions, where k_generate's direct stores are shorter:
 // 1000 records x 25 in 6.8 us against 11.5, 33 000 x 24 in 9.2 and 8.8, 65 000 x
-// 24 in 12.9 and 9.2.  Normals in rows of less than a step it beats for longer,
-// as it transforms only the fields that some lane wants: 105 000 x 3 in 7.9 us
-// and 9.8, 262 144 x 3 even.  Joined runs against each lane's own, at mixed
-// positions: 65 000 x 5 in 7.5 us and 6.0, 140 000 x 11 10.1 and 12.6.
-constexpr uint64_t ROWS_MIN = 1u << 15, ROWS_MIN_SHORT_NORMALS = 1u << 18;
+// 24 in 12.9 and 9.2; rows of more than a step and odd length, which cannot
+// leave in pairs, 33 000 x 25 in 9.6 us and 12.8, 65 000 x 25 in 13.4 and 14.0.
+// Normals in rows of less than a step k_generate draws faster for longer, as it
+// transforms only the fields that some lane wants: 90 000 x 3 in 7.2 us and 9.2,
+// 90 000 x 6 in 9.3 and 9.6, but 200 000 x 6 in 17.1 and 13.2, 131 072 x 9 in
+// 13.3 and 12.8.  Joined runs against each lane's own, at mixed positions:
+// 65 000 x 5 in 7.5 us and 6.0, 140 000 x 11 in 10.1 and 12.6.
+template <Out K>
+constexpr bool rows_kernel(uint64_t n, uint64_t count) {
+  if (count > ROWS_MAX_COUNT) return false;
+  if (K == Out::NORMAL && count < FIELDS) return n >= 1u << 17;
+  return n >= (count > FIELDS && count % 2 != 0 ? 1u << 16 : 1u << 15);
+}
 constexpr uint32_t ROWS_JOINED = 1u << 17;
 
 template <Out K, uint32_t T>
@@ -1465,8 +1473,7 @@ int generate_impl(rlx_state* states, uint64_t n, uint64_t count, void* out, uint
   const uint32_t lgs = lg < 6 ? lg : 6;
   const int writeback = lg <= 6;
   const bool mf = g_step_kind.load(std::memory_order_relaxed) == RLX_STEP_MFMA;
-  if (!TRACE && lgs == 0 && mf && !force_general && count <= ROWS_MAX_COUNT &&
-      n >= (K == Out::NORMAL && count < FIELDS ? ROWS_MIN_SHORT_NORMALS : ROWS_MIN)) {
+  if (!TRACE && lgs == 0 && mf && !force_general && rows_kernel<K>(n, count)) {
     if (count <= FIELDS) {
       k_generate_rows<K, 1><<<grid, BLOCK, 0, s>>>(states, (uint32_t)n, (uint32_t)count, o, t.P, p, err);
     } else {

@@ -66,7 +66,8 @@ def test_rows_of_many_records(n, count, start):
     assert rlx.check_errors() == 0
 
 
-@pytest.mark.parametrize("n,count", ((32768 + 65, 12), (32768 + 65, 25), (262144 + 1, 1), (262144 + 1, 7)))
+@pytest.mark.parametrize("n,count", ((32768 + 65, 12), (32768 + 65, 25), (65536 + 65, 25),
+                                     (262144 + 1, 1), (262144 + 1, 5), (262144 + 1, 7)))
 @pytest.mark.parametrize("start", (0, None))
 def test_normal_rows(n, count, start):
     st = records(n, start)
