@@ -405,7 +405,9 @@ __device__ __forceinline__ void mfma_step_split(uint32_t (&x)[NW], const Fetch0&
 // nothing moved a step of a lone wave takes 5% longer: 64 streams x 10 000 at 8
 // lanes 130 us against 124 (normals 248, 245 with LDS reads, 250 and spills with
 // MFMAs); 65 536 x 4096 is even.
-constexpr int MF_CROSS_ALL = 0x108, MF_CROSS_LDS = 0x100;
+// Operands through the L1 wait longer: 20 streams x 60 000 normals of several
+// levels at 64 lanes 220 us with LDS reads only, 180 with MFMAs and such reads.
+constexpr int MF_CROSS_ALL = 0x108, MF_CROSS_LDS = 0x100, MF_CROSS_BUFFER = 0x28;
 
 template <int CROSS = MF_CROSS_ALL, class Fetch>
 __device__ __forceinline__ void mfma_step_split(uint32_t (&x)[NW], const Fetch& fetch, bool force_general) {

@@ -773,6 +773,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(K == Out:
   const uint32_t l = (uint32_t)tid & ((1u << lg) - 1u);
 
   constexpr bool SHARED = LGS >= 5;  // as in k_generate
+  // normals with 64 lanes have the registers, at their 3 waves per SIMD
+  constexpr int LEVEL_CROSS = K == Out::NORMAL && LGS == 6 ? MF_CROSS_BUFFER : MF_CROSS_LDS;
   uint32_t x[NW];
   uint32_t pos = 0, sp = 0, w = 0;
   int li = -1;
@@ -853,7 +855,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(K == Out:
     if (__any(live && t + (1u << lg) <= nadv)) {
       if (LGS == 6 || (uniform && u0 == u1)) {
         // one level for the wave: one operand fetch serves both halves
-        mfma_step_split<MF_CROSS_LDS>(x, MfFromBuffer(level_ptr(L.M, u0) + (size_t)lg * MF_LEVEL_WORDS, threadIdx.x & 63), false);
+        mfma_step_split<LEVEL_CROSS>(x, MfFromBuffer(level_ptr(L.M, u0) + (size_t)lg * MF_LEVEL_WORDS, threadIdx.x & 63), false);
       } else if (SHARED || uniform) {
         mfma_step_split<false, 0>(x, MfFromBuffer(level_ptr(L.M, u0) + (size_t)lg * MF_LEVEL_WORDS, threadIdx.x & 63),
                                   MfFromBuffer(level_ptr(L.M, u1) + (size_t)lg * MF_LEVEL_WORDS, threadIdx.x & 63), false);
