@@ -1291,13 +1291,12 @@ namespace {
 std::atomic<uint32_t> g_lanes_override{0};
 std::atomic<int> g_step_kind{RLX_STEP_MFMA};
 
-// Nominal lanes per record (rlx_lanes_per_stream), and those that generate
-// calls with the vector-ALU step take: the largest power of two G <=
-// RLX_MAX_LANES such that the launch stays within `target` lanes and every
-// lane still takes at least `min_steps` generator steps -- or, while the
-// launch has fewer lanes than one wave per SIMD (2^16), at least one step.
-// 2^21 lanes and 8 steps with the matrix-core step, 2^20 and 16 with the
-// vector-ALU step.
+// Nominal lanes per record (rlx_lanes_per_stream), and those that calls with
+// the vector-ALU step take: the largest power of two G <= RLX_MAX_LANES such
+// that the launch stays within `target` lanes and every lane still takes at
+// least `min_steps` generator steps -- or, while the launch has fewer lanes
+// than one wave per SIMD (2^16), at least one step.  2^21 lanes and 8 steps with
+// the matrix-core step, 2^20 and 16 with the vector-ALU step.
 uint32_t nominal_lanes(uint64_t n, uint64_t count, bool mf) {
   const uint64_t steps = count / FIELDS + 1;
   const uint64_t target = mf ? 1ull << 21 : 1ull << 20, sparse = 1ull << 16;
@@ -1312,47 +1311,85 @@ uint32_t nominal_lanes(uint64_t n, uint64_t count, bool mf) {
   return (uint32_t)g;
 }
 
-// Lanes per record that generate calls with the matrix-core step take: the
-// power of two G with the smallest estimate (microseconds) of the launch's
-// time, up to 2^21 lanes.
-//  * Computing: a lane takes ceil(blocks / G) steps after a start-up worth
-//    3.5 steps (2..16 lanes: a generic product) or 2.75 (32 and more: shared
-//    by a half-wave; 1: none), and a step takes 1.15 us of latency or 0.65 us
-//    per wave that its SIMD holds, whichever is longer.
-//  * Storing: rates by the length of the runs a group writes (16 G bytes an
-//    instruction), measured over buffers larger than the last-level cache:
-//    2.6 TB/s (one lane, rows of more than two steps; 4.2 for shorter ones,
-//    kept whole) up to 6 TB/s for 32 lanes and more.
-//  * The longer of the two plus a third of the shorter; more than 64 lanes
-//    need a second launch, 5 us.  Among those, estimates within 5% go to more
-//    lanes.
-// Against the best G in sweeps of 60 shapes (1 to 2^20 records, 16 to 2^22
-// values) this is 0.8% slower on average; the nominal number is 5.2%: 5000 x 1001 took 21.5 us with 8
-// lanes, 15.5 with 32; 65 536 x 250 50 us with 2 lanes, 40 with 8; 2^18 x 128
-// 106 us with 1, 90 with 2.
-// Normals take 2.1 times a step's work (16 384 x 1000: 55 us with 8 lanes, 60
-// with 16).  Records of several levels (Draw::LEVELS) count 2 below 32 lanes:
-// there a half-wave may mix levels, and its lanes then each run a generic
-// product a step, 4 steps' worth (30 000 x 1000 over five levels: 94 us with
-// 8 lanes and 64 with 32 in no order, 58 and 65 sorted by level).
-enum class Draw { UNIFORM, NORMAL, LEVELS };
+// What a launch of one kind of draw costs, fitted as auto_lanes says.
+//   step     microseconds of a step with 1, 2, 3 and 4 waves on each SIMD; more
+//            waves take proportionally longer
+//   start    a lane's start-up in steps of the uniform kind: 2..16 lanes (a
+//            generic product), 32 and 64 (shared by a half-wave), more (by a
+//            wave); the legacy kernel's lanes always take a product each
+//   rate     TB/s that the rows are written at with 1, 2 and 4 lanes (runs of
+//            16 G bytes an instruction); 5.9 with 16 and 5.8 with 8 or more than 16
+//   mixed, alone  factors of `step` for 2..16 lanes and for one: with several
+//            levels a wave whose half mixes them runs a generic product a step
+//   values, traced  values per step, and further bytes written
+struct DrawCost {
+  double step[4], start[3], rate[3];
+  double mixed, alone;
+  uint32_t values, traced;
+};
+enum class Draw { UNIFORM, NORMAL, LEVELS, LEVELS_NORMAL, LEGACY, TRACED };
+constexpr DrawCost DRAW_COST[] = {
+    {{1.12, 1.46, 1.98, 2.95}, {1.7, 1.6, 1.2}, {2.35, 3.5, 4.4}, 1.0, 1.0, 12, 0},
+    {{2.15, 3.25, 4.6, 6.5}, {1.7, 1.6, 1.2}, {2.35, 3.5, 4.4}, 1.0, 1.0, 12, 0},
+    {{1.4, 1.65, 1.9, 2.6}, {1.7, 1.6, 1.2}, {2.35, 3.5, 4.4}, 1.7, 3.5, 12, 0},
+    {{2.45, 3.95, 5.3, 7.1}, {1.7, 1.6, 1.2}, {2.35, 3.5, 4.4}, 1.3, 1.5, 12, 0},
+    {{1.1, 1.5, 1.9, 2.5}, {1.7, 1.85, 1.6}, {1.6, 3.5, 4.2}, 1.0, 1.0, 11, 0},
+    {{1.0, 1.7, 2.0, 3.4}, {1.7, 1.2, 1.1}, {2.8, 4.4, 5.5}, 1.0, 1.0, 12, 72}};
+constexpr bool several_levels(Draw kind) { return kind == Draw::LEVELS || kind == Draw::LEVELS_NORMAL; }
 
-uint32_t auto_lanes_mfma(uint64_t n, uint64_t count, Draw kind) {
-  const double bytes = (double)n * (double)(count * 8 + sizeof(rlx_state) * 2) * 1e-6;  // at 1 TB/s: us
-  const uint64_t blocks = count / FIELDS + 1;
+// Lanes per record that generate calls with the matrix-core step take: the
+// power of two G with the smallest estimate of the launch's time, up to 2^21
+// lanes (and 64 with several levels: a record's lanes in one wave).
+//  * Computing: ceil(blocks / G) steps and the start-up, at the rate of the
+//    busiest SIMD.  One lane whose rows do not end on a step's boundary adds
+//    1.5 us.
+//  * Storing: the records at 4 TB/s and the rows at `rate` (6 TB/s for one lane
+//    with rows of up to two steps, which mostly leave as they are, rows_kernel);
+//    the more steps a wave takes, the further apart the rows that are being
+//    written, 1% a step.
+//  * The longer of the two plus a third of the shorter; more than 64 lanes
+//    need a second launch, 4.7 us.
+// Fitted to 2800 shapes (1 to 3 000 000 records, 4 to 2^22 values, uniform and
+// normal, into 1 GB of buffers in turn) with every G that is not hopeless: the
+// pick takes 0.9% (uniform) and 0.8% (normal) longer than the best on average,
+// which is what two timings of one launch differ by.  The estimate before it,
+// without the waves per SIMD and the spread of long waves, took 9% (uniform) and
+// 5% (normal) longer: 2100 x 50 000 with 64 lanes 216 us against 172 with 512,
+// normals 10 000 x 4096 with 16 lanes 144 us against 120 with 32.  The nominal
+// number: 11 and 15%.  Where 8 and 16 lanes are close, rows that don't end with
+// a line are sometimes better off with 8: 78 000 x 713 in 98 us, 107 with 16.
+// For several levels (336 shapes, each in level blocks and in no order, which
+// the rule cannot know) 1.2%: 30 000 x 1000 over five levels takes 62 us in
+// blocks and 65 in no order with the 32 lanes picked, with 8 lanes 54 and 88.
+// Legacy and traced draws 0.6%; with the uniform costs 2100 x 50 000 legacy
+// doubles took 235 us, 191 so, and 32 768 x 30 traced 14.5 us, 11.8.
+uint32_t auto_lanes(uint64_t n, uint64_t count, Draw kind) {
+  const DrawCost& cost = DRAW_COST[(int)kind];
+  const bool levels = several_levels(kind), plain = kind == Draw::UNIFORM || kind == Draw::NORMAL;
+  const uint64_t blocks = count / cost.values + 1;
+  // microseconds: the records' traffic, and the rows' bytes at 1 TB/s
+  const double records = (double)n * (sizeof(rlx_state) * 2) * 1e-6 / 4;
+  const double rows = (double)n * ((double)count * 8 + (double)(cost.traced * blocks)) * 1e-6;
+  const bool whole = count % FIELDS == 0;
   double best = 0;
   uint64_t pick = 1;
-  for (uint64_t g = 1; g <= RLX_MAX_LANES && (g == 1 || (g <= 2 * blocks && n <= (1ull << 21) / g)); g *= 2) {
-    const double waves = (double)n * (double)g / 65536.0;
-    const double each = kind == Draw::NORMAL ? 2.1 : kind == Draw::LEVELS && g < 32 ? 2.0 : 1.0;
-    const double steps = each * (double)((blocks + g - 1) / g) + (g == 1 ? 0.0 : g < 32 ? 3.5 : 2.75);
-    const double compute = steps * (waves * 0.65 > 1.15 ? waves * 0.65 : 1.15) + (g > 64 ? 5.0 : 0.0);
-    const double rate = g == 1 ? (count <= 2 * FIELDS ? 4.2 : 2.6) : g == 2 ? 3.2 : g == 4 ? 3.8 : g == 8 ? 5.0
-                        : g == 16 ? 5.6 : 6.0;
-    const double store = bytes / rate;
-    const double t = compute > store ? compute + store / 3 : store + compute / 3;
-    if (g == 1 || t < best || (pick > 64 && t < 1.05 * best)) {
-      if (g == 1 || t < best) best = t;
+  for (uint64_t g = 1; g <= (levels ? 64u : RLX_MAX_LANES) && (g == 1 || (g <= 2 * blocks && n <= (1ull << 21) / g));
+       g *= 2) {
+    const double load = (double)((n * g + 255) / 256) / 256.0;     // waves per SIMD
+    const int w = load > 3 ? 3 : load > 2 ? 2 : load > 1 ? 1 : 0;  // the busiest SIMD's, less 1
+    const double full = load / 4;  // a last round that is nearly empty takes a little longer than its share
+    const double rounds = full > 1 ? full + 0.04 * ((double)(uint64_t)(full + 0.999) - full) : 1;
+    const double steps = (double)((blocks + g - 1) / g);
+    const double start = g == 1 ? 0 : cost.start[g < 32 ? 0 : g <= 64 ? 1 : 2];
+    const double factor = g == 1 ? cost.alone : g < 32 ? cost.mixed : 1;
+    const double compute = rounds * (steps * factor * cost.step[w] + start * DRAW_COST[0].step[w] +
+                                     (g == 1 && plain && !whole ? 1.5 : 0));
+    const double rate = g == 1 && plain && count <= 2 * FIELDS ? 6.0
+                        : g <= 4 ? cost.rate[g / 2] : g == 16 ? 5.9 : 5.8;
+    const double store = records + rows / rate * (g == 1 ? 1 : 1 + 0.01 * steps);
+    const double t = (compute > store ? compute + store / 3 : store + compute / 3) + (g > 64 ? 4.7 : 0);
+    if (g == 1 || t < best) {
+      best = t;
       pick = g;
     }
   }
@@ -1360,24 +1397,23 @@ uint32_t auto_lanes_mfma(uint64_t n, uint64_t count, Draw kind) {
 }
 
 uint32_t lanes_for(uint64_t n, uint64_t count, Draw kind) {
-  const uint32_t o = g_lanes_override.load(std::memory_order_relaxed);
-  if (o) return o;
-  return g_step_kind.load(std::memory_order_relaxed) == RLX_STEP_MFMA ? auto_lanes_mfma(n, count, kind)
-                                                                       : nominal_lanes(n, count, false);
+  uint32_t g = g_lanes_override.load(std::memory_order_relaxed);
+  if (g == 0)
+    g = g_step_kind.load(std::memory_order_relaxed) == RLX_STEP_MFMA ? auto_lanes(n, count, kind)
+                                                                     : nominal_lanes(n, count, false);
+  return several_levels(kind) && g > 64 ? 64 : g;
 }
 
 // Argument checks shared by the generate calls; on success *lg is log2 of
 // the lanes per record and *grid covers n << lg lanes.
 int generate_args(const rlx_state* states, uint64_t n, uint64_t count, const void* out, uint32_t p,
                   uint32_t* lg, dim3* grid, Draw kind) {
-  const bool record_levels = kind == Draw::LEVELS;
   if (!states || !out) return RLX_EINVAL;
-  if (record_levels ? p != RLX_P_RECORD : !valid_p(p)) return RLX_EINVAL;
+  if (several_levels(kind) ? p != RLX_P_RECORD : !valid_p(p)) return RLX_EINVAL;
   if (!aligned(states, 16) || !aligned(out, 8)) return RLX_EINVAL;
   if (n > RLX_MAX_STREAMS || count > RLX_MAX_COUNT) return RLX_EINVAL;
   if (count > UINT64_MAX / 8 / n) return RLX_EINVAL;
-  uint32_t G = lanes_for(n, count, kind);
-  if (record_levels && G > 64) G = 64;  // a record's lanes in one wave
+  const uint32_t G = lanes_for(n, count, kind);
   *lg = (uint32_t)__builtin_ctz(G);
   if (n > (UINT64_MAX >> *lg)) return RLX_EINVAL;
   return grid_for(n << *lg, grid) ? RLX_OK : RLX_EINVAL;
@@ -1424,7 +1460,8 @@ int generate_levels_impl(rlx_state* states, uint64_t n, uint64_t count, void* ou
   if (n == 0 || count == 0) return RLX_OK;
   uint32_t lg;
   dim3 grid;
-  int rc = generate_args(states, n, count, out, RLX_P_RECORD, &lg, &grid, Draw::LEVELS);
+  int rc = generate_args(states, n, count, out, RLX_P_RECORD, &lg, &grid,
+                         K == Out::NORMAL ? Draw::LEVELS_NORMAL : Draw::LEVELS);
   if (rc) return rc;
   hipStream_t s = as_stream(stream);
   LevelSet L;
@@ -1456,7 +1493,8 @@ int generate_impl(rlx_state* states, uint64_t n, uint64_t count, void* out, uint
   if (n == 0 || count == 0) return RLX_OK;
   uint32_t lg;
   dim3 grid;
-  int rc = generate_args(states, n, count, out, p, &lg, &grid, K == Out::NORMAL ? Draw::NORMAL : Draw::UNIFORM);
+  int rc = generate_args(states, n, count, out, p, &lg, &grid,
+                         TRACE ? Draw::TRACED : K == Out::NORMAL ? Draw::NORMAL : Draw::UNIFORM);
   if (rc) return rc;
   if (TRACE) {
     if (!trace || !aligned(trace, 8)) return RLX_EINVAL;
@@ -1504,7 +1542,7 @@ int generate_lcg52_impl(rlx_state* states, uint64_t n, uint64_t count, double* o
   if (n == 0 || count == 0) return RLX_OK;
   uint32_t lg;
   dim3 grid;
-  int rc = generate_args(states, n, count, out, p, &lg, &grid, Draw::UNIFORM);
+  int rc = generate_args(states, n, count, out, p, &lg, &grid, Draw::LEGACY);
   if (rc) return rc;
   hipStream_t s = as_stream(stream);
   Tables t;
@@ -1751,10 +1789,8 @@ uint32_t rlx_lanes_per_stream(uint64_t n, uint64_t count) {
 }
 
 uint32_t rlx_call_lanes(int kind, uint64_t n, uint64_t count) {
-  if (kind < RLX_DRAW_UNIFORM || kind > RLX_DRAW_TRACED) return 0;
-  const bool levels = kind == RLX_DRAW_LEVELS || kind == RLX_DRAW_LEVELS_NORMAL;
-  const uint32_t g = lanes_for(n, count, levels ? Draw::LEVELS : kind == RLX_DRAW_NORMAL ? Draw::NORMAL : Draw::UNIFORM);
-  return levels && g > 64 ? 64 : g;
+  static_assert((int)Draw::UNIFORM == RLX_DRAW_UNIFORM && (int)Draw::TRACED == RLX_DRAW_TRACED);
+  return kind < RLX_DRAW_UNIFORM || kind > RLX_DRAW_TRACED ? 0 : lanes_for(n, count, (Draw)kind);
 }
 
 int rlx_set_step_kernel(int kind) {

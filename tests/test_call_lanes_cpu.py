@@ -38,6 +38,18 @@ def test_shapes_that_other_tests_mean():
     assert rlx.call_lanes("uniform", 65536, 4096) == 32   # the kernel that the profiles are of
 
 
+# shapes where the estimate without the waves per SIMD, or with the uniform
+# draw's costs for all, took far too few or too many lanes: the least and the
+# most lanes within 5% of the best measured
+@pytest.mark.parametrize("kind,n,count,least,most", (
+    ("uniform", 2100, 50000, 512, 1024), ("uniform", 4200, 25000, 256, 512), ("uniform", 8192, 10000, 64, 128),
+    ("normal", 10000, 4096, 32, 32), ("normal", 25000, 4096, 16, 32),
+    ("legacy", 2100, 50000, 256, 1024), ("traced", 32768, 30, 2, 4), ("legacy", 500000, 30, 2, 4),
+    ("levels", 8192, 1000, 32, 32), ("levels", 6500, 4000, 32, 64), ("levels", 65536, 4096, 32, 64)))
+def test_picks(kind, n, count, least, most):
+    assert least <= rlx.call_lanes(kind, n, count) <= most
+
+
 def test_unknown_kinds():
     lib = rlx.lib()
     assert lib.rlx_call_lanes(-1, 5, 10) == 0 and lib.rlx_call_lanes(6, 5, 10) == 0
