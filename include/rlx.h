@@ -510,10 +510,12 @@ int rlx_test_engine(rlx_state *states, uint64_t n, uint64_t count,
                     double *out, uint32_t mode, uint32_t p, void *stream);
 
 /* out[i] = A_p^(2^g) x[i] mod m: one generator step by 2^g steps (g <
- * RLX_FOLD_G) with the step kernel `kind` (RLX_STEP_MFMA or RLX_STEP_VALU)
- * that the generate calls use, on arbitrary x[i] < m (sections 2.1, 2.2).
- * general != 0 sends the final fold through its general branch.  Lanes past
- * n run on x = 1 and store nothing. */
+ * RLX_FOLD_G) on arbitrary x[i] < m (sections 2.1, 2.2), with RLX_STEP_VALU by
+ * the step that the generate calls take with that kernel, with RLX_STEP_MFMA by
+ * the device engine's matrix-core step and, for the steps of up to 2^16 that
+ * the generate calls take, by theirs too: a row on which the two differ is all
+ * ones.  general != 0 sends the final fold through its general branch.  Lanes
+ * past n run on x = 1 and store nothing. */
 int rlx_test_step(const uint64_t *x, uint64_t *out, uint64_t n, uint32_t p,
                   uint32_t g, int kind, int general, void *stream);
 

@@ -584,7 +584,8 @@ def test_pow(base: torch.Tensor, exps: torch.Tensor) -> torch.Tensor:
 
 def test_step(x: torch.Tensor, p: int, g: int, kind: int = STEP_MFMA, general: bool = False) -> torch.Tensor:
     """One generator step by 2^g steps (A_p^(2^g) x mod m) with the given
-    step kernel, on int64 [n, 9] states x < m."""
+    step kernel, on int64 [n, 9] states x < m; a row is all ones where the
+    generate calls' matrix-core step (g < 17) and the device engine's differ."""
     n = _need_words(x, None, "x")
     out = torch.empty_like(x)
     with torch.cuda.device(x.device):

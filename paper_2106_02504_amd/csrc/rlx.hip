@@ -1102,13 +1102,16 @@ __global__ __launch_bounds__(BLOCK) void k_test_to_ranlux(const uint64_t* __rest
   carry[i] = ranlux_carry(x, d);
 }
 
-// One step by the folded multiplier of 2^g steps, with either step kernel,
-// on arbitrary states (the matrix-core step needs whole waves: lanes past n
-// step x = 1 and store nothing).
+// One step by the folded multiplier of 2^g steps, with either step kernel, on
+// arbitrary states (the matrix-core step needs whole waves: lanes past n step
+// x = 1 and store nothing).  Where there are operands of the split form (ptab),
+// which the generate kernels use, both forms run, and a state on which they
+// differ is stored as all ones.
 template <bool MF>
 __global__ __launch_bounds__(BLOCK) void k_test_step(const uint64_t* __restrict__ xs, uint64_t* __restrict__ out,
                                                      uint64_t n, const uint32_t* __restrict__ ctab,
-                                                     const uint32_t* __restrict__ mtab, int general) {
+                                                     const uint32_t* __restrict__ mtab,
+                                                     const uint32_t* __restrict__ ptab, int general) {
   const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
   uint32_t x[NW];
   if (i < n) {
@@ -1118,9 +1121,23 @@ __global__ __launch_bounds__(BLOCK) void k_test_step(const uint64_t* __restrict_
   }
   if constexpr (MF) {
     __shared__ mf_v4i af[MF_FRAGS * 64];
+    uint32_t y[NW];
+#pragma unroll
+    for (int k = 0; k < NW; ++k) y[k] = x[k];
     mf_stage_operands(af, mtab, threadIdx.x, BLOCK);
     __syncthreads();
     mfma_step(x, MfFromArray{af, threadIdx.x & 63}, general != 0);
+    if (ptab) {
+      __syncthreads();
+      mf_stage_operands(af, ptab, threadIdx.x, BLOCK);
+      __syncthreads();
+      mfma_step_split(y, MfFromArray{af, threadIdx.x & 63}, general != 0);
+      uint32_t differ = 0;
+#pragma unroll
+      for (int k = 0; k < NW; ++k) differ |= x[k] ^ y[k];
+#pragma unroll
+      for (int k = 0; k < NW; ++k) x[k] = differ ? 0xFFFFFFFFu : y[k];
+    }
   } else {
     step(x, constant_table(ctab), general != 0, SgprBarrier());
   }
@@ -1845,10 +1862,11 @@ int rlx_test_step(const uint64_t* x, uint64_t* out, uint64_t n, uint32_t p, uint
   if (rc) return rc;
   const uint32_t* ct = t.C + (size_t)g * FOLD_ROW_WORDS;
   const uint32_t* mt = t.M + (size_t)g * MF_LEVEL_WORDS;
+  const uint32_t* pt = g < (uint32_t)MF_SPLIT_STEPS ? t.P + (size_t)g * MF_LEVEL_WORDS : nullptr;
   if (kind == RLX_STEP_MFMA) {
-    k_test_step<true><<<grid, BLOCK, 0, s>>>(x, out, n, ct, mt, general);
+    k_test_step<true><<<grid, BLOCK, 0, s>>>(x, out, n, ct, mt, pt, general);
   } else {
-    k_test_step<false><<<grid, BLOCK, 0, s>>>(x, out, n, ct, mt, general);
+    k_test_step<false><<<grid, BLOCK, 0, s>>>(x, out, n, ct, mt, pt, general);
   }
   return launch_status();
 }
