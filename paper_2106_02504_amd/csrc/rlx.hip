@@ -314,11 +314,11 @@ __device__ __forceinline__ uint64_t skip_steps(uint32_t& pos, uint64_t k, int by
 // lane may handle any of them.  A refused record (of another level, say, which
 // a call on another stream may be skipping meanwhile) is not written at all:
 // its copy's level is spoilt, and a wave stores the records whose copies have
-// level p.  2^20 records by log-uniform offsets: 129 us
-// with strided record accesses, 117 so, at 5 waves per SIMD both (by one offset:
-// 99 us, 91; 131 072 records: 23.2 and 14.7, 21.6 and 13.2).  What is left is
-// vector issue, about 75 us of it, beside 300 MB of window entries from beyond
-// the L2.
+// level p.  2^20 records by log-uniform offsets, calls back to back over several
+// sets of records (one set again and again takes 96 us): 129 us with strided
+// record accesses, 117 so, at 5 waves per SIMD both (by one offset: 99 us, 91;
+// 131 072 records: 23.2 and 14.7, 21.6 and 13.2).  What is left is vector issue,
+// about 75 us of it, beside 300 MB of window entries from beyond the L2.
 __global__ __launch_bounds__(BLOCK) void k_skip(rlx_state* __restrict__ st, uint64_t n,
                                                 const uint64_t* __restrict__ steps, uint64_t steps0,
                                                 uint32_t p, const uint32_t* __restrict__ W,
@@ -592,8 +592,12 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(K == Out:
 // (T = 2, 51 us instead of 65 at 24 values before rows were kept whole); with
 // up to 12 the smaller stage (T = 1) leaves twice the waves (2^20 x 12: 63 us
 // against 80).  Rows that end within the kept steps go out as the one run of
-// whole lines they are, for any count and positions.  With T = 1 records take
-// one step or none: those that took it leave through LDS at the end whatever
+// whole lines they are, for any count and positions: 24 and 12 values of records
+// at position 0, 20 (positions 0, 8, 4) on two calls of three, 2^19 x 20 in 40
+// us.  A wave with one record that goes on into the next run stores each run's
+// parts of the rows: 2^19 x 24 at one other position 47 to 55 us (40 at 0), at
+// mixed ones 64, x 20 57, 2^20 x 12 72 (46 at 0).  With T = 1 records take one
+// step or none: those that took it leave through LDS at the end whatever
 // their positions, of the others only the position is written (2^20 x 1 at
 // mixed positions 51.5 us with whole records stored by their lanes, 37.4 so).
 constexpr uint64_t ROWS_MAX_COUNT = 1ull << 20;  // 32-bit byte offsets within a wave's 64 rows
@@ -678,7 +682,12 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(T == 1 ? 
         wave_sync();
         if (__all(mine && ps + count <= RUN)) {
           // the rows' values are all here: the wave's rows are one run of
-          // 512 count bytes on a 512-byte boundary of the output
+          // 512 count bytes, 512-byte steps from the output's start.  Whole lines
+          // by non-temporal stores; where `out` is not on a line's boundary the
+          // run's lines are split between two instructions and these are still
+          // no slower than plain ones: 2^20 x 12 at 0, 16 and 64 bytes 45.3, 46.7
+          // and 45.7 us, plain 47.9, 48.9 and 48.3; 2^19 x 24 40.8, 41.8 and 39.1,
+          // plain 43.1, 42.2 and 41.5.
           const uint32_t magic = (uint32_t)(0x100000000ull / count) + 1u;  // i / count = i magic >> 32 for i < 64 count
           for (uint32_t e0 = 0; e0 < 32u * count; e0 += 64u) {
             // every lane takes part in the exchange of positions; the last

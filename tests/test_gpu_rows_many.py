@@ -104,3 +104,11 @@ def test_few_records_at_mixed_positions_cost_no_more():
             times.append(e0.elapsed_time(e1) * 50)
         return statistics.median(times[2:])
     assert us(None) < 1.35 * us(0)
+
+
+@pytest.mark.parametrize("count,offset", ((12, 2), (13, 6), (24, 2), (24, 8)))
+def test_whole_rows_off_a_line(count, offset):
+    # outputs on 16-byte boundaries inside a line
+    st = records(49152 + 1, 0)
+    a, b = (draws("f64", st.clone(), count, lanes, offset) for lanes in (1, 2))
+    assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
